@@ -51,7 +51,7 @@ struct rip_replicas {
   int64_t numel0 = 0;      // elements of segment 0 (the whole range when flat)
   bool has_grad = false, has_mom = false;
   int64_t tiles[rip::kTileOptions] = {};  // tiles per unit, by slot option
-  void* dmem = nullptr;  // ptab [3][S][N] u64 | seg_numel [S] i64 | seg_tile0 [4][S+1] i64
+  void* dmem = nullptr;  // ptab [S][N][3] u64 | seg_numel [S] i64 | seg_tile0 [4][S+1] i64
   // Handles from rip_replicas_create_noalloc keep their tables in the
   // device's fixed table array instead of dmem; `generation` tells whether
   // a later such handle on the same device has overwritten them.
@@ -293,9 +293,9 @@ int32_t create_replicas(int32_t n_replicas, int32_t n_segments, int32_t dtype,
         src = (size_t)r * n_segments + s0;
       }
       const size_t dst = (size_t)s * N + r;
-      ptab[dst] = reinterpret_cast<uint64_t>(param[src]);
-      ptab[(size_t)S * N + dst] = grad ? reinterpret_cast<uint64_t>(grad[src]) : 0;
-      ptab[(size_t)2 * S * N + dst] = mom ? reinterpret_cast<uint64_t>(mom[src]) : 0;
+      ptab[3 * dst] = reinterpret_cast<uint64_t>(param[src]);
+      ptab[3 * dst + 1] = grad ? reinterpret_cast<uint64_t>(grad[src]) : 0;
+      ptab[3 * dst + 2] = mom ? reinterpret_cast<uint64_t>(mom[src]) : 0;
     }
   }
   // First tile of every segment, for each tile size (1, 2, 4, 8 slots).
@@ -508,9 +508,6 @@ int32_t build_step(const rip_replicas* r, const int32_t* group_offsets, const in
     a.unit_work0[u + 1] = (uint32_t)work;
   }
   a.work = (uint32_t)work;
-  a.uniform_tiles = units > 0 ? a.unit_work0[1] : 0;
-  for (int32_t u = 1; u < units && a.uniform_tiles; ++u)
-    if (a.unit_work0[u + 1] - a.unit_work0[u] != a.uniform_tiles) a.uniform_tiles = 0;
   a.flat_numel = r->n_seg == 1 ? r->numel0 : 0;
   shapes.n = units;
   for (int32_t u = 0; u < units; ++u) {
@@ -520,6 +517,18 @@ int32_t build_step(const rip_replicas* r, const int32_t* group_offsets, const in
     for (int32_t j = 0; j < shapes.k[u]; ++j) shapes.act[u] += is_active[a.member[b + j]];
   }
   return RIP_OK;
+}
+
+// Sets the grid of a launch: one row of workgroups per unit when all units
+// have the same tile count and every tile gets a workgroup (the kernel then
+// needs no search for its unit), else one row of at most max_blocks
+// workgroups, which loop over the work items beyond it.
+void set_grid(rip::StepArgs& a, uint32_t max_blocks) {
+  a.blocks = a.work < max_blocks ? a.work : max_blocks;
+  if (a.work > max_blocks) return;
+  for (int32_t u = 1; u < a.n_units; ++u)
+    if (a.unit_work0[u + 1] - a.unit_work0[u] != a.unit_work0[1]) return;
+  a.blocks = 0;
 }
 
 // The launch of the units u with part[u] == which, in their order: the
@@ -538,9 +547,6 @@ void subset_step(const rip::StepArgs& a, const uint8_t* part, int which, rip::St
   out.n_units = n;
   out.work = work;
   out.uniform_k = 0;  // the units no longer sit at base = unit * k
-  out.uniform_tiles = n > 0 ? out.unit_work0[1] : 0;
-  for (int32_t u = 1; u < n && out.uniform_tiles; ++u)
-    if (out.unit_work0[u + 1] - out.unit_work0[u] != out.uniform_tiles) out.uniform_tiles = 0;
 }
 
 }  // namespace
@@ -569,13 +575,13 @@ extern "C" int32_t rip_preduce(const rip_replicas* r, const int32_t* group_offse
       rip::g_max_blocks.load() > 0 ? rip::g_max_blocks.load() : rip::kDefaultMaxBlocks;
   const int forced_bpc = rip::g_blocks_per_cu.load();
   const bool ext = a.wd != 0.0f || a.nesterov != 0;
-  auto launch = [&](const rip::StepArgs& x, int waves) -> int32_t {
+  auto launch = [&](rip::StepArgs& x, int waves) -> int32_t {
     if (x.work == 0) return RIP_OK;
-    const int blocks = (int)(x.work < (uint32_t)max_blocks ? x.work : (uint32_t)max_blocks);
+    set_grid(x, (uint32_t)max_blocks);
     const int bpc = forced_bpc > 0 ? forced_bpc : waves * 64 / rip::kBlock;
     size_t lds = 0;
     if (bpc > 0 && r->lds_per_cu > 0) lds = (size_t)(r->lds_per_cu / bpc) & ~(size_t)255;
-    const hipError_t le = rip::launch_fused_step(x, r->dtype == RIP_BF16, mom, ext, blocks, lds,
+    const hipError_t le = rip::launch_fused_step(x, r->dtype == RIP_BF16, mom, ext, lds,
                                                  static_cast<hipStream_t>(stream));
     if (le != hipSuccess) return rip::fail(RIP_E_HIP, "kernel launch: %s", hipGetErrorString(le));
     ++rip::g_last_launches;

@@ -35,13 +35,14 @@ constexpr int slot_log2(int k, bool mom) {
 // Passed by value as the kernel argument (about 2.6 KiB), so each launch
 // carries its own schedule and no device staging buffer is needed.
 struct StepArgs {
-  const uint64_t* ptab;       // device [3][S][N]: param, grad, mom pointers
+  const uint64_t* ptab;       // device [S][N][3]: param, grad, mom pointers
   const int64_t* seg_numel;   // device [S]
   const int64_t* seg_tile0;   // device [kTileOptions][S + 1]: first tile of each
                               // segment, for tiles of 1, 2, 4, 8 slots
   int32_t n_seg, n_rep, n_units;
   uint32_t work;              // work items (tiles) of all units
-  uint32_t uniform_tiles;     // tiles per unit when all units have the same count, else 0
+  uint32_t blocks;            // workgroups of a one-row grid; 0: the grid has one row of
+                              // work / n_units workgroups per unit (equal tile counts)
   uint32_t uniform_k;         // members per unit when all units have the same size, else 0
   int64_t flat_numel;         // elements of the only segment when n_seg == 1
   float lr, mu, wd;
@@ -68,7 +69,7 @@ static_assert(RIP_MAX_REPLICAS <= 256, "unit_info packs member indices into 8 bi
 
 // ext: weight decay or Nesterov momentum is on (the kernel variant that
 // handles them; the plain variant leaves them out of the arithmetic).
-hipError_t launch_fused_step(const StepArgs& a, bool bf16, bool mom, bool ext, int blocks,
-                             size_t lds_bytes, hipStream_t stream);
+hipError_t launch_fused_step(const StepArgs& a, bool bf16, bool mom, bool ext, size_t lds_bytes,
+                             hipStream_t stream);
 
 }  // namespace rip

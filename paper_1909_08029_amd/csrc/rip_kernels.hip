@@ -43,12 +43,12 @@ namespace {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-// Replica buffers are plain device memory: the element-wise path (ragged
-// tails) accesses them through the global address space so the compiler
-// emits global_* (not flat_*) instructions.
+// Replica buffers are plain device memory: the single elements of ragged
+// ends are accessed through the global address space so the compiler emits
+// global_* (not flat_*) instructions.
 #define RIP_GLOBAL __attribute__((address_space(1)))
 
-// Full tiles are accessed through buffer instructions, non-temporal (every
+// Tiles are accessed through buffer instructions, non-temporal (every
 // byte is touched once per step): a descriptor per member stream whose base
 // is the tile's first byte and whose size is the tile's bytes, and a
 // per-lane offset of at most a few KB.  On gfx950 this form streamed 3-4%
@@ -61,9 +61,8 @@ typedef __amdgpu_buffer_rsrc_t Rsrc;
 constexpr int kRsrcWord3 = 0x00020000;  // raw (untyped) buffer, 32-bit data format
 constexpr int kNonTemporal = 2;         // cache-policy operand: nt
 
-__device__ __forceinline__ Rsrc tile_rsrc(const char* base, int64_t tile_byte, int bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base) + tile_byte, 0, bytes,
-                                           kRsrcWord3);
+__device__ __forceinline__ Rsrc tile_rsrc(const char* tile, int bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(tile), 0, bytes, kRsrcWord3);
 }
 __device__ __forceinline__ u32x4 bld16(Rsrc r, int off) {
   return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, kNonTemporal);
@@ -181,7 +180,7 @@ struct Vec<true> {
   }
 };
 
-// Scalar element access for tails and the generic (k > 8) path.
+// Single-element access for ragged ends.
 template <bool BF16>
 __device__ __forceinline__ float ld1(const char* base, int64_t e) {
   if constexpr (BF16)
@@ -237,68 +236,112 @@ __device__ __forceinline__ float update(float w, float g, float& v, const Opt& o
   }
 }
 
+// Launch-wide values, read once per workgroup before anything else.
+struct Header {
+  const RIP_CONST uint64_t* ptab;
+  const RIP_CONST int64_t *seg_numel, *seg_tile0;
+  uint32_t work, blocks, uniform_k;
+  int n_seg, n_rep, n_units;
+  int64_t flat_numel;
+  Opt opt;
+};
+
 struct Members {
   char* w[kMaxK];
   const char* g[kMaxK];
   char* v[kMaxK];
-  bool act[kMaxK];
+  uint32_t act;  // update flags, bit j = member j
+  __device__ __forceinline__ bool active(int j) const {
+    return __builtin_expect((act >> j) & 1u, 1);
+  }
 };
 
 // The unit's member ids (one per byte of `ids`) came with the unit; their
-// pointers are 3K independent scalar loads, all issued before one wait.
+// table entries are independent scalar loads, all issued before one wait.
 template <int K, bool MOM>
-__device__ __forceinline__ void load_members(const StepArgs& a, uint64_t ids, uint32_t act8,
+__device__ __forceinline__ void load_members(const Header& h, uint64_t ids, uint32_t act8,
                                              int seg, Members& m) {
-  const int plane = a.n_seg * a.n_rep;
 #pragma unroll
   for (int j = 0; j < K; ++j) {
     const int id = (int)((ids >> (8 * j)) & 0xFFu);
-    const int idx = seg * a.n_rep + id;
-    m.w[j] = reinterpret_cast<char*>(cld(a.ptab, idx));
-    m.g[j] = reinterpret_cast<const char*>(cld(a.ptab, plane + idx));
-    m.v[j] = reinterpret_cast<char*>(cld(a.ptab, 2 * plane + idx));
-    m.act[j] = (act8 >> j) & 1u;
+    const RIP_CONST uint64_t* e = h.ptab + (uint32_t)(seg * h.n_rep + id) * 3u;
+    m.w[j] = reinterpret_cast<char*>(e[0]);
+    m.g[j] = reinterpret_cast<const char*>(e[1]);
+    if constexpr (MOM) m.v[j] = reinterpret_cast<char*>(e[2]);
   }
+  m.act = act8;
   // Materialize every member's pointers and flag here, so one wait covers
   // all of these scalar loads.  Left alone, the compiler sinks each pointer
   // load next to its use, and every vector load then waits for its own
   // scalar round trip: the wave's loads go out one at a time.
 #pragma unroll
   for (int j = 0; j < K; ++j) {
-    asm volatile("" ::"s"(m.w[j]), "s"(m.g[j]), "s"((int)m.act[j]));
+    asm volatile("" ::"s"(m.w[j]), "s"(m.g[j]));
     if constexpr (MOM) asm volatile("" ::"s"(m.v[j]));
   }
 }
 
-// U consecutive 16-byte slots of a full tile for a unit of K members; the
-// tile starts `tile_byte` bytes into every member stream.
-template <int K, int U, bool BF16, bool MOM, bool EXT>
-__device__ __forceinline__ void tile_slots(const Members& m, int64_t tile_byte, const Opt& o) {
+// U consecutive 16-byte slots of a tile for a unit of K members; the tile
+// starts `tile_byte` bytes into every member stream.
+//
+// RAGGED: the last, partial tile of a segment, `bytes` long.  It runs the
+// same code with its descriptors' sizes cut to the whole 16-byte vectors that
+// are left, so the hardware drops what lies beyond (loads give 0, stores
+// write nothing, no access straddles the end), and the fewer than N elements
+// after them go one per lane.  Those loads are issued together with the
+// vectors', so a ragged end costs one memory round trip.  (Element by
+// element, each member's loads after the last one's, it held its wave for
+// tens of microseconds: 16 fp32 replicas of 304,327 with momentum, weight
+// decay and groups of four 20.5 us a step, now 19.1, and 18.4 with a size
+// that ends on a tile; the same as 59 separate tensors 21.7, now 20.0.)
+template <int K, int U, bool BF16, bool MOM, bool EXT, bool RAGGED>
+__device__ __forceinline__ void tile_slots(Members& m, int64_t tile_byte, int bytes,
+                                           const Opt& o) {
   using V = Vec<BF16>;
   constexpr int N = V::N;
   constexpr float inv_k = (float)(1.0 / K);
   constexpr int kTileBytes = U * kBlock * 16;
+  int vec_bytes = RAGGED ? bytes & ~15 : kTileBytes;
   int off[U];  // this lane's byte offset of each slot within the tile
 #pragma unroll
   for (int u = 0; u < U; ++u) off[u] = (u * kBlock + (int)threadIdx.x) * 16;
-  Rsrc rw[K], rg[K], rv[K];
 #pragma unroll
   for (int j = 0; j < K; ++j) {
-    rw[j] = tile_rsrc(m.w[j], tile_byte, kTileBytes);
-    rg[j] = tile_rsrc(m.g[j], tile_byte, kTileBytes);
-    if constexpr (MOM) rv[j] = tile_rsrc(m.v[j], tile_byte, kTileBytes);
+    m.w[j] += tile_byte;
+    m.g[j] += tile_byte;
+    if constexpr (MOM) m.v[j] += tile_byte;
+  }
+  // The elements after the last whole vector (RAGGED).
+  const int64_t e1 = vec_bytes / (BF16 ? 2 : 4) + (int)threadIdx.x;
+  const bool has1 = RAGGED && e1 < bytes / (BF16 ? 2 : 4);
+  float w1[K], g1[K], v1[K];
+  if (has1) {
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+      w1[j] = ld1<BF16>(m.w[j], e1);
+      if (m.active(j)) {
+        g1[j] = ld1<BF16>(m.g[j], e1);
+        if constexpr (MOM) v1[j] = ld1<BF16>(m.v[j], e1);
+      }
+    }
   }
   u32x4 wv[U][K], gv[U][K], vv[U][K];
 #pragma unroll
   for (int u = 0; u < U; ++u)
 #pragma unroll
     for (int j = 0; j < K; ++j) {
-      wv[u][j] = bld16(rw[j], off[u]);
-      if (m.act[j]) {
-        gv[u][j] = bld16(rg[j], off[u]);
-        if constexpr (MOM) vv[u][j] = bld16(rv[j], off[u]);
+      wv[u][j] = bld16(tile_rsrc(m.w[j], vec_bytes), off[u]);
+      if (m.active(j)) {
+        gv[u][j] = bld16(tile_rsrc(m.g[j], vec_bytes), off[u]);
+        if constexpr (MOM) vv[u][j] = bld16(tile_rsrc(m.v[j], vec_bytes), off[u]);
       }
     }
+  // From here on the flags and the descriptors' size are new values to the
+  // compiler: a descriptor (four scalar registers) lives for its loads only
+  // and is put together again for its stores, and a flag is tested where it
+  // is used.  Kept over the whole function, up to 24 descriptors and as many
+  // branch masks overflowed the scalar registers into VGPR lanes.
+  asm volatile("" : "+s"(m.act), "+s"(vec_bytes));
   // All arithmetic comes before the first store.  Stores count against the
   // same vmcnt as loads, and because the gradient and momentum loads are
   // conditional (active members only) the compiler's waits before each
@@ -306,6 +349,16 @@ __device__ __forceinline__ void tile_slots(const Members& m, int64_t tile_byte, 
   // members would make the next wait cover that store's completion, a full
   // write round trip.  (A straight-line variant for groups whose members all
   // update, with exact waits, measured no faster and slowed bf16 by 2%.)
+  float s1;
+  if constexpr (RAGGED) {
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+      float x = w1[j];
+      if (m.active(j)) x = update<MOM, EXT>(x, g1[j], v1[j], o);
+      s1 = (j == 0) ? x : s1 + x;
+    }
+    if constexpr (K > 1) s1 = s1 * inv_k;
+  }
   u32x4 out[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) {
@@ -314,7 +367,7 @@ __device__ __forceinline__ void tile_slots(const Members& m, int64_t tile_byte, 
     for (int j = 0; j < K; ++j) {
       float x[N];
       V::unpack(wv[u][j], x);
-      if (m.act[j]) {
+      if (m.active(j)) {
         float g[N], v[N];
         V::unpack(gv[u][j], g);
         if constexpr (MOM) V::unpack(vv[u][j], v);
@@ -333,38 +386,46 @@ __device__ __forceinline__ void tile_slots(const Members& m, int64_t tile_byte, 
   }
   // Keep the instruction scheduler from sinking arithmetic below the stores.
   __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" : "+s"(m.act));
   if constexpr (MOM) {
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
       for (int j = 0; j < K; ++j)
-        if (m.act[j]) bst16(rv[j], off[u], vv[u][j]);
+        if (m.active(j)) bst16(tile_rsrc(m.v[j], vec_bytes), off[u], vv[u][j]);
   }
 #pragma unroll
   for (int u = 0; u < U; ++u)
 #pragma unroll
-    for (int j = 0; j < K; ++j) bst16(rw[j], off[u], out[u]);
+    for (int j = 0; j < K; ++j) bst16(tile_rsrc(m.w[j], vec_bytes), off[u], out[u]);
+  if (has1) {
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+      if constexpr (MOM)
+        if (m.active(j)) st1<BF16>(m.v[j], e1, v1[j]);
+      st1<BF16>(m.w[j], e1, s1);
+    }
+  }
 }
 
-// Element-wise path for a partial tile (any k): each thread walks elements
-// e0 + i*stride below `end`.
+// Element-wise path for the partial tile of a group larger than kMaxK: each
+// thread walks elements e0 + i*stride below `end`.
 template <bool BF16, bool MOM, bool EXT>
-__device__ void elementwise(const StepArgs& a, int base, int k, int seg, int64_t begin,
+__device__ void elementwise(const Header& h, int base, int k, int seg, int64_t begin,
                             int64_t end) {
-  const int plane = a.n_seg * a.n_rep;
   const float inv_k = kInv.v[k];
-  const Opt o{a.lr, a.mu, a.wd, a.nesterov != 0};
+  const Opt& o = h.opt;
   for (int64_t e = begin + threadIdx.x; e < end; e += kBlock) {
     float s = 0.0f;
     for (int j = 0; j < k; ++j) {
       const int id = cld8(kargs().member, base + j);
-      const int idx = seg * a.n_rep + id;
-      char* w = reinterpret_cast<char*>(cld(a.ptab, idx));
+      const RIP_CONST uint64_t* t = h.ptab + (uint32_t)(seg * h.n_rep + id) * 3u;
+      char* w = reinterpret_cast<char*>(t[0]);
       float x = ld1<BF16>(w, e);
       if ((cld(kargs().active_bits, id >> 5) >> (id & 31)) & 1u) {
-        const float g = ld1<BF16>(reinterpret_cast<const char*>(cld(a.ptab, plane + idx)), e);
+        const float g = ld1<BF16>(reinterpret_cast<const char*>(t[1]), e);
         if constexpr (MOM) {
-          char* vp = reinterpret_cast<char*>(cld(a.ptab, 2 * plane + idx));
+          char* vp = reinterpret_cast<char*>(t[2]);
           float v = ld1<BF16>(vp, e);
           x = update<true, EXT>(x, g, v, o);
           st1<BF16>(vp, e, v);
@@ -378,7 +439,7 @@ __device__ void elementwise(const StepArgs& a, int base, int k, int seg, int64_t
     if (k > 1) s = s * inv_k;
     for (int j = 0; j < k; ++j) {
       const int id = cld8(kargs().member, base + j);
-      st1<BF16>(reinterpret_cast<char*>(cld(a.ptab, seg * a.n_rep + id)), e, s);
+      st1<BF16>(reinterpret_cast<char*>(h.ptab[(uint32_t)(seg * h.n_rep + id) * 3u]), e, s);
     }
   }
 }
@@ -390,13 +451,12 @@ __device__ void elementwise(const StepArgs& a, int base, int k, int seg, int64_t
 // member.  Each member's w, g and v are read once and written once, as in
 // the specialized paths; only the member pointers are fetched twice.
 template <bool BF16, bool MOM, bool EXT>
-__device__ __forceinline__ void wide_tile(const StepArgs& a, int base, int k, int seg,
+__device__ __forceinline__ void wide_tile(const Header& h, int base, int k, int seg,
                                           int64_t e_tile) {
   using V = Vec<BF16>;
   constexpr int N = V::N;
   constexpr int C = kMaxK;  // members per chunk
-  const int plane = a.n_seg * a.n_rep;
-  const Opt o{a.lr, a.mu, a.wd, a.nesterov != 0};
+  const Opt& o = h.opt;
   const int64_t tile_byte = e_tile * (BF16 ? 2 : 4);
   constexpr int kTileBytes = kBlock * 16;
   const int off = (int)threadIdx.x * 16;
@@ -410,11 +470,11 @@ __device__ __forceinline__ void wide_tile(const StepArgs& a, int base, int k, in
 #pragma unroll
     for (int jj = 0; jj < C; ++jj) {
       const int id = (int)((ids >> (8 * jj)) & 0xFFu);
-      const int idx = seg * a.n_rep + id;
+      const RIP_CONST uint64_t* e = h.ptab + (uint32_t)(seg * h.n_rep + id) * 3u;
       const bool in = j0 + jj < k;
-      w[jj] = in ? reinterpret_cast<char*>(cld(a.ptab, idx)) : nullptr;
-      g[jj] = in ? reinterpret_cast<const char*>(cld(a.ptab, plane + idx)) : nullptr;
-      v[jj] = in && MOM ? reinterpret_cast<char*>(cld(a.ptab, 2 * plane + idx)) : nullptr;
+      w[jj] = in ? reinterpret_cast<char*>(e[0]) : nullptr;
+      g[jj] = in ? reinterpret_cast<const char*>(e[1]) : nullptr;
+      v[jj] = in && MOM ? reinterpret_cast<char*>(e[2]) : nullptr;
       act[jj] = in && ((cld(kargs().active_bits, id >> 5) >> (id & 31)) & 1u);
     }
 #pragma unroll
@@ -425,9 +485,9 @@ __device__ __forceinline__ void wide_tile(const StepArgs& a, int base, int k, in
     Rsrc rw[C], rg[C], rv[C];
 #pragma unroll
     for (int jj = 0; jj < C; ++jj) {
-      rw[jj] = tile_rsrc(w[jj], tile_byte, kTileBytes);
-      rg[jj] = tile_rsrc(g[jj], tile_byte, kTileBytes);
-      if constexpr (MOM) rv[jj] = tile_rsrc(v[jj], tile_byte, kTileBytes);
+      rw[jj] = tile_rsrc(w[jj] + tile_byte, kTileBytes);
+      rg[jj] = tile_rsrc(g[jj] + tile_byte, kTileBytes);
+      if constexpr (MOM) rv[jj] = tile_rsrc(v[jj] + tile_byte, kTileBytes);
     }
     u32x4 wv[C], gv[C], vv[C];
 #pragma unroll
@@ -474,13 +534,15 @@ __device__ __forceinline__ void wide_tile(const StepArgs& a, int base, int k, in
 #pragma unroll
     for (int jj = 0; jj < C; ++jj) {
       const int id = (int)((ids >> (8 * jj)) & 0xFFu);
-      w[jj] = j0 + jj < k ? reinterpret_cast<char*>(cld(a.ptab, seg * a.n_rep + id)) : nullptr;
+      w[jj] = j0 + jj < k
+                  ? reinterpret_cast<char*>(h.ptab[(uint32_t)(seg * h.n_rep + id) * 3u])
+                  : nullptr;
     }
 #pragma unroll
     for (int jj = 0; jj < C; ++jj) asm volatile("" ::"s"(w[jj]));
 #pragma unroll
     for (int jj = 0; jj < C; ++jj)
-      if (j0 + jj < k) bst16(tile_rsrc(w[jj], tile_byte, kTileBytes), off, out);
+      if (j0 + jj < k) bst16(tile_rsrc(w[jj] + tile_byte, kTileBytes), off, out);
   }
 }
 
@@ -502,20 +564,12 @@ struct Unit {
   uint64_t ids;   // member ids 0..7, one per byte
 };
 
-// Launch-wide values, read once per workgroup before anything else.
-struct Header {
-  uint32_t work, uniform_tiles, uniform_k;
-  int n_seg;
-  int64_t flat_numel;
-};
-
 // One tile of a unit of K members (K <= kMaxK, or 0 for the element-wise path
 // with any k).  The tile geometry is a compile-time constant here, so a
 // workgroup reaches its first vector load after a handful of scalar
 // instructions: a flat handle needs no segment search at all.
 template <int K, bool BF16, bool MOM, bool EXT>
-__device__ __forceinline__ void unit_tile(const StepArgs& a, const Header& h, const Unit& u,
-                                          int64_t tile) {
+__device__ __forceinline__ void unit_tile(const Header& h, const Unit& u, int64_t tile) {
   constexpr int O = slot_log2(K == 0 ? kMaxK + 1 : K, MOM);
   constexpr int SL = 1 << O;
   constexpr int N = Vec<BF16>::N;
@@ -526,54 +580,70 @@ __device__ __forceinline__ void unit_tile(const StepArgs& a, const Header& h, co
     e_tile = tile * TE;
     numel = h.flat_numel;
   } else {
-    const int64_t* tile0 = a.seg_tile0 + O * (h.n_seg + 1);
+    const RIP_CONST int64_t* tile0 = h.seg_tile0 + O * (h.n_seg + 1);
     seg = last_le(tile0, h.n_seg, tile);
     e_tile = (tile - cld(tile0, seg)) * TE;
-    numel = cld(a.seg_numel, seg);
+    numel = cld(h.seg_numel, seg);
   }
   if constexpr (K > 0) {
-    if (e_tile + TE <= numel) {
-      constexpr int esize = BF16 ? 2 : 4;
-      Members m;
-      load_members<K, MOM>(a, u.ids, u.act8, seg, m);
-      tile_slots<K, SL, BF16, MOM, EXT>(m, e_tile * esize, Opt{a.lr, a.mu, a.wd, a.nesterov != 0});
-      return;
+    constexpr int esize = BF16 ? 2 : 4;
+    Members m;
+    if (__builtin_expect(e_tile + TE <= numel, 1)) {
+      load_members<K, MOM>(h, u.ids, u.act8, seg, m);
+      tile_slots<K, SL, BF16, MOM, EXT, false>(m, e_tile * esize, 0, h.opt);
+    } else {
+      load_members<K, MOM>(h, u.ids, u.act8, seg, m);
+      tile_slots<K, SL, BF16, MOM, EXT, true>(m, e_tile * esize, (int)(numel - e_tile) * esize,
+                                              h.opt);
     }
   } else {
     if (e_tile + TE <= numel) {
-      wide_tile<BF16, MOM, EXT>(a, u.base, u.k, seg, e_tile);
+      wide_tile<BF16, MOM, EXT>(h, u.base, u.k, seg, e_tile);
       return;
     }
+    elementwise<BF16, MOM, EXT>(h, u.base, u.k, seg, e_tile, numel);
   }
-  const int64_t end = (e_tile + TE < numel) ? e_tile + TE : numel;
-  elementwise<BF16, MOM, EXT>(a, u.base, u.k, seg, e_tile, end);
 }
 
 template <bool BF16, bool MOM, bool EXT>
-__global__ __launch_bounds__(kBlock) void fused_step_kernel(StepArgs a) {
-  // Load the whole header into scalar registers in one batch up front: left
-  // to itself the compiler spreads it over several batches (and loads
-  // flat_numel late, through a select of addresses), and every extra batch is
-  // one more dependent scalar round trip before the workgroup's first vector
-  // load.
-  const Header h{a.work, a.uniform_tiles, a.uniform_k, a.n_seg, a.flat_numel};
-  asm volatile("" ::"s"(h.work), "s"(h.uniform_tiles), "s"(h.uniform_k), "s"(h.n_seg),
-               "s"(h.flat_numel), "s"(a.ptab), "s"(a.n_rep), "s"(a.lr), "s"(a.mu), "s"(a.wd),
-               "s"(a.nesterov), "s"(a.n_units), "s"(a.seg_numel), "s"(a.seg_tile0));
-  for (uint32_t w = blockIdx.x; w < h.work; w += gridDim.x) {
+__global__ __launch_bounds__(kBlock) void fused_step_kernel(StepArgs) {
+  uint32_t w = blockIdx.x;
+  for (;;) {
+    // The argument's address is hidden from the optimizer anew for every work
+    // item, so nothing is computed ahead of the loop.  A workgroup almost
+    // always runs one item (it loops only above the workgroup limit), and
+    // values hoisted for all sizes of unit, most of them spilled to VGPR
+    // lanes, delayed every wave's first load (two replicas of 16,384: 2.27 us
+    // a launch, now 1.93, of which an empty kernel takes 1.65).
+    KArgs* a = &kargs();
+    asm volatile("" : "+s"(a));
+    // Load the whole header into scalar registers in one batch up front: left
+    // to itself the compiler spreads it over several batches (and loads
+    // flat_numel late, through a select of addresses), and every extra batch is
+    // one more dependent scalar round trip before the workgroup's first vector
+    // load.
+    const Header h{(const RIP_CONST uint64_t*)a->ptab, (const RIP_CONST int64_t*)a->seg_numel,
+                   (const RIP_CONST int64_t*)a->seg_tile0, a->work, a->blocks, a->uniform_k, a->n_seg,
+                   a->n_rep, a->n_units, a->flat_numel,
+                   Opt{a->lr, a->mu, a->wd, a->nesterov != 0}};
+    asm volatile("" ::"s"(h.ptab), "s"(h.seg_numel), "s"(h.seg_tile0), "s"(h.work), "s"(h.blocks), "s"(h.uniform_k), "s"(h.n_seg),
+                 "s"(h.n_rep), "s"(h.n_units), "s"(h.flat_numel), "s"(h.opt.lr), "s"(h.opt.mu),
+                 "s"(h.opt.wd), "s"((int)h.opt.nesterov));
+    // A launch of units with the same tile count has a grid of one row per
+    // unit; otherwise the grid is one row of work items, unit after unit.
     int unit;
     int64_t tile;
-    if (h.uniform_tiles) {  // every unit has the same tile count
-      unit = (int)(w / h.uniform_tiles);
-      tile = (int64_t)(w - (uint32_t)unit * h.uniform_tiles);
+    if (h.blocks == 0) {
+      unit = (int)blockIdx.y;
+      tile = (int64_t)w;
     } else {
-      unit = last_le(kargs().unit_work0, a.n_units, w);
-      tile = (int64_t)(w - cld(kargs().unit_work0, unit));
+      unit = last_le(a->unit_work0, h.n_units, w);
+      tile = (int64_t)(w - cld(a->unit_work0, unit));
     }
     // With equal-sized units the member window's address needs no load, so
     // it is fetched together with the unit's info word: the unit costs one
     // scalar round trip, its members' pointers a second.
-    const uint32_t info = cld(kargs().unit_info, unit);
+    const uint32_t info = cld(a->unit_info, unit);
     Unit u;
     if (h.uniform_k) {
       u.k = (int)h.uniform_k;
@@ -583,18 +653,21 @@ __global__ __launch_bounds__(kBlock) void fused_step_kernel(StepArgs a) {
       u.base = (int)unit_info_base(info);
     }
     u.act8 = unit_info_act8(info);
-    u.ids = cld8x8(kargs().member, u.base);
+    u.ids = cld8x8(a->member, u.base);
     switch (u.k) {
-      case 1: unit_tile<1, BF16, MOM, EXT>(a, h, u, tile); break;
-      case 2: unit_tile<2, BF16, MOM, EXT>(a, h, u, tile); break;
-      case 3: unit_tile<3, BF16, MOM, EXT>(a, h, u, tile); break;
-      case 4: unit_tile<4, BF16, MOM, EXT>(a, h, u, tile); break;
-      case 5: unit_tile<5, BF16, MOM, EXT>(a, h, u, tile); break;
-      case 6: unit_tile<6, BF16, MOM, EXT>(a, h, u, tile); break;
-      case 7: unit_tile<7, BF16, MOM, EXT>(a, h, u, tile); break;
-      case 8: unit_tile<8, BF16, MOM, EXT>(a, h, u, tile); break;
-      default: unit_tile<0, BF16, MOM, EXT>(a, h, u, tile); break;
+      case 1: unit_tile<1, BF16, MOM, EXT>(h, u, tile); break;
+      case 2: unit_tile<2, BF16, MOM, EXT>(h, u, tile); break;
+      case 3: unit_tile<3, BF16, MOM, EXT>(h, u, tile); break;
+      case 4: unit_tile<4, BF16, MOM, EXT>(h, u, tile); break;
+      case 5: unit_tile<5, BF16, MOM, EXT>(h, u, tile); break;
+      case 6: unit_tile<6, BF16, MOM, EXT>(h, u, tile); break;
+      case 7: unit_tile<7, BF16, MOM, EXT>(h, u, tile); break;
+      case 8: unit_tile<8, BF16, MOM, EXT>(h, u, tile); break;
+      default: unit_tile<0, BF16, MOM, EXT>(h, u, tile); break;
     }
+    if (h.blocks == 0) return;
+    w += h.blocks;
+    if (w >= h.work) return;
   }
 }
 
@@ -608,15 +681,16 @@ const void* kernel_for(bool ext) {
 }
 }  // namespace
 
-hipError_t launch_fused_step(const StepArgs& a, bool bf16, bool mom, bool ext, int blocks,
-                             size_t lds_bytes, hipStream_t stream) {
+hipError_t launch_fused_step(const StepArgs& a, bool bf16, bool mom, bool ext, size_t lds_bytes,
+                             hipStream_t stream) {
   const void* fn = bf16 ? (mom ? kernel_for<true, true>(ext) : kernel_for<true, false>(ext))
                         : (mom ? kernel_for<false, true>(ext) : kernel_for<false, false>(ext));
   void* args[] = {const_cast<StepArgs*>(&a)};
   // hipLaunchKernel reports this launch's own status (not an earlier sticky error).
   // lds_bytes is a reservation only (the kernel uses no LDS): it caps how
   // many workgroups share a CU.
-  return hipLaunchKernel(fn, dim3(blocks), dim3(kBlock), args, lds_bytes, stream);
+  const dim3 grid = a.blocks ? dim3(a.blocks) : dim3(a.work / a.n_units, a.n_units);
+  return hipLaunchKernel(fn, grid, dim3(kBlock), args, lds_bytes, stream);
 }
 
 }  // namespace rip
