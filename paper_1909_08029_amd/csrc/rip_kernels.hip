@@ -246,6 +246,34 @@ struct Header {
   Opt opt;
 };
 
+// The last element of a bf16 tile of odd size: the low half of a dword that
+// the tile's descriptors leave out (so the vector's dword holds 0).  It is in
+// slot e / 64 of lane e % 64, e its vector.
+constexpr int kOutside = 0x7FFFFFF0;  // a byte offset past every tile
+
+template <int U, typename F>
+__device__ __forceinline__ void odd_load(const char* tile, int bytes, F&& vec) {
+  const int at = bytes - 2, e = at >> 4, word = (at >> 2) & 3;
+  const int off = (e & (kBlock - 1)) == (int)threadIdx.x ? at : kOutside;
+  const uint32_t x = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(tile_rsrc(tile, bytes), off, 0,
+                                                                    kNonTemporal);
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) vec(u)[i] |= (u == e / kBlock && i == word) ? x : 0u;
+}
+template <int U, typename F>
+__device__ __forceinline__ void odd_store(char* tile, int bytes, F&& vec) {
+  const int at = bytes - 2, e = at >> 4, word = (at >> 2) & 3;
+  const int off = (e & (kBlock - 1)) == (int)threadIdx.x ? at : kOutside;
+  uint32_t x = 0;
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x = (u == e / kBlock && i == word) ? vec(u)[i] : x;
+  __builtin_amdgcn_raw_buffer_store_b16((uint16_t)x, tile_rsrc(tile, bytes), off, 0, kNonTemporal);
+}
+
 struct Members {
   char* w[kMaxK];
   const char* g[kMaxK];
@@ -281,27 +309,25 @@ __device__ __forceinline__ void load_members(const Header& h, uint64_t ids, uint
   }
 }
 
-// U consecutive 16-byte slots of a tile for a unit of K members; the tile
-// starts `tile_byte` bytes into every member stream.
+// Up to U consecutive 16-byte slots of a tile for a unit of K members; the
+// tile starts `tile_byte` bytes into every member stream and holds `bytes`
+// (the last tile of a segment: what is left of it).
 //
-// RAGGED: the last, partial tile of a segment, `bytes` long.  It runs the
-// same code with its descriptors' sizes cut to the whole 16-byte vectors that
-// are left, so the hardware drops what lies beyond (loads give 0, stores
-// write nothing, no access straddles the end), and the fewer than N elements
-// after them go one per lane.  Those loads are issued together with the
-// vectors', so a ragged end costs one memory round trip.  (Element by
-// element, each member's loads after the last one's, it held its wave for
-// tens of microseconds: 16 fp32 replicas of 304,327 with momentum, weight
-// decay and groups of four 20.5 us a step, now 19.1, and 18.4 with a size
-// that ends on a tile; the same as 59 separate tensors 21.7, now 20.0.)
-template <int K, int U, bool BF16, bool MOM, bool EXT, bool RAGGED>
+// A ragged end needs no code of its own: the descriptors end at the last
+// whole dword, and the hardware checks each dword of an access against that
+// (a dword beyond loads as 0 and is not stored).  Only a bf16 segment of odd
+// size has an element left after that, which the lane of its vector loads and
+// stores by itself.  (Element by element, each member's loads after the last
+// one's, a ragged tile held its wave for tens of microseconds: 16 fp32
+// replicas of 304,327 with momentum, weight decay and groups of four 20.5 us
+// a step, now 19.1, and 18.4 with a size that ends on a tile; the same as 59
+// separate tensors 21.7, now 20.0.)
+template <int K, int U, bool BF16, bool MOM, bool EXT>
 __device__ __forceinline__ void tile_slots(Members& m, int64_t tile_byte, int bytes,
                                            const Opt& o) {
   using V = Vec<BF16>;
   constexpr int N = V::N;
   constexpr float inv_k = (float)(1.0 / K);
-  constexpr int kTileBytes = U * kBlock * 16;
-  int vec_bytes = RAGGED ? bytes & ~15 : kTileBytes;
   int off[U];  // this lane's byte offset of each slot within the tile
 #pragma unroll
   for (int u = 0; u < U; ++u) off[u] = (u * kBlock + (int)threadIdx.x) * 16;
@@ -311,37 +337,36 @@ __device__ __forceinline__ void tile_slots(Members& m, int64_t tile_byte, int by
     m.g[j] += tile_byte;
     if constexpr (MOM) m.v[j] += tile_byte;
   }
-  // The elements after the last whole vector (RAGGED).
-  const int64_t e1 = vec_bytes / (BF16 ? 2 : 4) + (int)threadIdx.x;
-  const bool has1 = RAGGED && e1 < bytes / (BF16 ? 2 : 4);
-  float w1[K], g1[K], v1[K];
-  if (has1) {
-#pragma unroll
-    for (int j = 0; j < K; ++j) {
-      w1[j] = ld1<BF16>(m.w[j], e1);
-      if (m.active(j)) {
-        g1[j] = ld1<BF16>(m.g[j], e1);
-        if constexpr (MOM) v1[j] = ld1<BF16>(m.v[j], e1);
-      }
-    }
-  }
+  const bool odd = BF16 && (bytes & 2);
   u32x4 wv[U][K], gv[U][K], vv[U][K];
 #pragma unroll
   for (int u = 0; u < U; ++u)
 #pragma unroll
     for (int j = 0; j < K; ++j) {
-      wv[u][j] = bld16(tile_rsrc(m.w[j], vec_bytes), off[u]);
+      wv[u][j] = bld16(tile_rsrc(m.w[j], bytes & ~3), off[u]);
       if (m.active(j)) {
-        gv[u][j] = bld16(tile_rsrc(m.g[j], vec_bytes), off[u]);
-        if constexpr (MOM) vv[u][j] = bld16(tile_rsrc(m.v[j], vec_bytes), off[u]);
+        gv[u][j] = bld16(tile_rsrc(m.g[j], bytes & ~3), off[u]);
+        if constexpr (MOM) vv[u][j] = bld16(tile_rsrc(m.v[j], bytes & ~3), off[u]);
       }
     }
+  if constexpr (BF16) {
+    if (__builtin_expect(odd, 0)) {
+#pragma unroll
+      for (int j = 0; j < K; ++j) {
+        odd_load<U>(m.w[j], bytes, [&](int u) -> u32x4& { return wv[u][j]; });
+        if (m.active(j)) {
+          odd_load<U>(m.g[j], bytes, [&](int u) -> u32x4& { return gv[u][j]; });
+          if constexpr (MOM) odd_load<U>(m.v[j], bytes, [&](int u) -> u32x4& { return vv[u][j]; });
+        }
+      }
+    }
+  }
   // From here on the flags and the descriptors' size are new values to the
   // compiler: a descriptor (four scalar registers) lives for its loads only
   // and is put together again for its stores, and a flag is tested where it
   // is used.  Kept over the whole function, up to 24 descriptors and as many
   // branch masks overflowed the scalar registers into VGPR lanes.
-  asm volatile("" : "+s"(m.act), "+s"(vec_bytes));
+  asm volatile("" : "+s"(m.act), "+s"(bytes));
   // All arithmetic comes before the first store.  Stores count against the
   // same vmcnt as loads, and because the gradient and momentum loads are
   // conditional (active members only) the compiler's waits before each
@@ -349,16 +374,6 @@ __device__ __forceinline__ void tile_slots(Members& m, int64_t tile_byte, int by
   // members would make the next wait cover that store's completion, a full
   // write round trip.  (A straight-line variant for groups whose members all
   // update, with exact waits, measured no faster and slowed bf16 by 2%.)
-  float s1;
-  if constexpr (RAGGED) {
-#pragma unroll
-    for (int j = 0; j < K; ++j) {
-      float x = w1[j];
-      if (m.active(j)) x = update<MOM, EXT>(x, g1[j], v1[j], o);
-      s1 = (j == 0) ? x : s1 + x;
-    }
-    if constexpr (K > 1) s1 = s1 * inv_k;
-  }
   u32x4 out[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) {
@@ -392,18 +407,20 @@ __device__ __forceinline__ void tile_slots(Members& m, int64_t tile_byte, int by
     for (int u = 0; u < U; ++u)
 #pragma unroll
       for (int j = 0; j < K; ++j)
-        if (m.active(j)) bst16(tile_rsrc(m.v[j], vec_bytes), off[u], vv[u][j]);
+        if (m.active(j)) bst16(tile_rsrc(m.v[j], bytes & ~3), off[u], vv[u][j]);
   }
 #pragma unroll
   for (int u = 0; u < U; ++u)
 #pragma unroll
-    for (int j = 0; j < K; ++j) bst16(tile_rsrc(m.w[j], vec_bytes), off[u], out[u]);
-  if (has1) {
+    for (int j = 0; j < K; ++j) bst16(tile_rsrc(m.w[j], bytes & ~3), off[u], out[u]);
+  if constexpr (BF16) {
+    if (__builtin_expect(odd, 0)) {
 #pragma unroll
-    for (int j = 0; j < K; ++j) {
-      if constexpr (MOM)
-        if (m.active(j)) st1<BF16>(m.v[j], e1, v1[j]);
-      st1<BF16>(m.w[j], e1, s1);
+      for (int j = 0; j < K; ++j) {
+        if constexpr (MOM)
+          if (m.active(j)) odd_store<U>(m.v[j], bytes, [&](int u) { return vv[u][j]; });
+        odd_store<U>(m.w[j], bytes, [&](int u) { return out[u]; });
+      }
     }
   }
 }
@@ -588,14 +605,9 @@ __device__ __forceinline__ void unit_tile(const Header& h, const Unit& u, int64_
   if constexpr (K > 0) {
     constexpr int esize = BF16 ? 2 : 4;
     Members m;
-    if (__builtin_expect(e_tile + TE <= numel, 1)) {
-      load_members<K, MOM>(h, u.ids, u.act8, seg, m);
-      tile_slots<K, SL, BF16, MOM, EXT, false>(m, e_tile * esize, 0, h.opt);
-    } else {
-      load_members<K, MOM>(h, u.ids, u.act8, seg, m);
-      tile_slots<K, SL, BF16, MOM, EXT, true>(m, e_tile * esize, (int)(numel - e_tile) * esize,
-                                              h.opt);
-    }
+    load_members<K, MOM>(h, u.ids, u.act8, seg, m);
+    const int bytes = (int)(e_tile + TE <= numel ? TE : numel - e_tile) * esize;
+    tile_slots<K, SL, BF16, MOM, EXT>(m, e_tile * esize, bytes, h.opt);
   } else {
     if (e_tile + TE <= numel) {
       wide_tile<BF16, MOM, EXT>(h, u.base, u.k, seg, e_tile);
