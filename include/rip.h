@@ -29,8 +29,8 @@
  *  - Handles are not thread-safe; use one handle per thread or lock.
  *  - Graph capture: rip_local_step and rip_preduce enqueue one kernel
  *    launch (two for a step that mixes unit shapes with far-apart residency
- *    preferences; nothing when the step has no work), each with its part of
- *    the step -- schedule, optimizer scalars, the handle's pointer table --
+ *    preferences, or groups above eight with other units; nothing when the
+ *    step has no work), each with its part of the step -- schedule, optimizer scalars, the handle's pointer table --
  *    in the kernel argument, and no memset, copy or allocation.  They may be
  *    called on a stream under HIP graph capture; each replay re-applies the
  *    captured step to whatever the buffers hold then.  The replicas handle
@@ -73,7 +73,7 @@ const char* rip_last_error(void);
 int32_t rip_abi_version(void);
 /* Kernel launches the calling thread's last rip_preduce, rip_local_step or
  * rip_step enqueued: 0 (an error before any launch, or a step with no work),
- * 1, or 2 (a step split by residency preference; see rip_preduce).  For
+ * 1, or 2 (a step split by its units' sizes; see rip_preduce).  For
  * accounting and tests; results never depend on it. */
 int32_t rip_last_launch_count(void);
 
@@ -298,11 +298,12 @@ int32_t rip_local_step(const rip_replicas* r, const int32_t* active, int32_t n_a
  * of the `n_groups` groups given as CSR (group g = members[group_offsets[g]
  * .. group_offsets[g+1]-1], strictly ascending).  Groups must be disjoint
  * (RIP_E_OVERLAP otherwise).  sgd == NULL is pure P-Reduce; then n_active
- * must be 0.  One kernel launch covers all groups and updates, or, when the
- * step's units prefer residency caps far apart (a Global Division step of
- * pairs and groups of eight, say) and no cap is forced with
- * rip_set_blocks_per_cu, two launches in a row on `stream`, each at its own
- * cap; the units are disjoint, so the result is the same either way.  If the
+ * must be 0.  One kernel launch covers all groups and updates, or two in a row
+ * on `stream`: when the step's units prefer residency caps far apart (a Global
+ * Division step of pairs and groups of eight, say) and no cap is forced with
+ * rip_set_blocks_per_cu, or when it has groups above eight, which run on a
+ * kernel of their own, beside others in more than a small launch.  The units
+ * are disjoint, so the result is the same either way.  If the
  * second of two launches fails, the first has been enqueued (RIP_E_HIP).
  * Errors: RIP_E_INVAL (also: the current device is not the handle's),
  * RIP_E_OVERLAP, RIP_E_UNSUPPORTED (a step of 2^31 or more tiles), RIP_E_HIP
@@ -337,7 +338,8 @@ int32_t rip_step(rip_sched* s, const rip_replicas* r, int64_t step, const uint8_
  * workgroups, beyond which workgroups loop over tiles); rip_set_blocks_per_cu
  * caps how many of the kernel's workgroups share a compute unit (0 = the
  * default: chosen per launch from its units' sizes, whether their members
- * update, and momentum, 4-14 per compute unit).  Negative values are
+ * update, and momentum, 4-14 per compute unit; 1-10 of the several-wave
+ * workgroups of groups above eight).  Negative values are
  * RIP_E_INVAL.  Results never depend on these settings. */
 int32_t rip_set_max_blocks(int32_t max_blocks);
 int32_t rip_set_blocks_per_cu(int32_t blocks_per_cu);

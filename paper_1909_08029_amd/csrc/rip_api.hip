@@ -111,7 +111,9 @@ extern "C" int32_t rip_set_max_blocks(int32_t max_blocks) {
 
 namespace {
 
-static_assert(rip::policy::kMaxK == rip::kMaxK, "launch policy and kernel disagree on kMaxK");
+static_assert(rip::policy::kMaxK == rip::kMaxK && rip::policy::kWideWaves == rip::kWideWaves &&
+                  rip::policy::kWideC == rip::kWideC && rip::kBlock == 64,
+              "launch policy and kernel disagree");
 
 int elems_per_16b(int32_t dtype) { return dtype == RIP_BF16 ? 8 : 4; }
 int elem_size(int32_t dtype) { return dtype == RIP_BF16 ? 2 : 4; }
@@ -476,8 +478,8 @@ int32_t build_step(const rip_replicas* r, const int32_t* group_offsets, const in
       unit_off.push_back(pos);
       ++units;
     }
-  for (int32_t id = 0; id < N; ++id)
-    if (is_active[id]) a.active_bits[id >> 5] |= 1u << (id & 31);
+  for (int32_t i = 0; i < pos; ++i)
+    if (is_active[a.member[i]]) a.member_act[i >> 5] |= 1u << (i & 31);
   for (int32_t u = 0; u < units; ++u) {
     const int32_t b = unit_off[u], k = unit_off[u + 1] - b;
     uint32_t act8 = 0;
@@ -575,31 +577,68 @@ extern "C" int32_t rip_preduce(const rip_replicas* r, const int32_t* group_offse
       rip::g_max_blocks.load() > 0 ? rip::g_max_blocks.load() : rip::kDefaultMaxBlocks;
   const int forced_bpc = rip::g_blocks_per_cu.load();
   const bool ext = a.wd != 0.0f || a.nesterov != 0;
-  auto launch = [&](rip::StepArgs& x, int waves) -> int32_t {
+  auto launch = [&](rip::StepArgs& x, int wide_waves, int per_cu) -> int32_t {
     if (x.work == 0) return RIP_OK;
     set_grid(x, (uint32_t)max_blocks);
-    const int bpc = forced_bpc > 0 ? forced_bpc : waves * 64 / rip::kBlock;
-    size_t lds = 0;
-    if (bpc > 0 && r->lds_per_cu > 0) lds = (size_t)(r->lds_per_cu / bpc) & ~(size_t)255;
-    const hipError_t le = rip::launch_fused_step(x, r->dtype == RIP_BF16, mom, ext, lds,
-                                                 static_cast<hipStream_t>(stream));
+    const int bpc = forced_bpc > 0 ? forced_bpc : per_cu;
+    const size_t share = r->lds_per_cu > 0 ? (size_t)(r->lds_per_cu / bpc) & ~(size_t)255 : 0;
+    const hipError_t le = rip::launch_step(x, r->dtype == RIP_BF16, mom, ext, wide_waves, share,
+                                           static_cast<hipStream_t>(stream));
     if (le != hipSuccess) return rip::fail(RIP_E_HIP, "kernel launch: %s", hipGetErrorString(le));
     ++rip::g_last_launches;
     return RIP_OK;
   };
+  uint8_t part[RIP_MAX_REPLICAS];
+  rip::StepArgs a0, a1;
+  // Groups above kMaxK run on a kernel of their own.  A step that also has
+  // other units is two launches, each at its own units' cap, or, while one
+  // launch of all units on that kernel is small, one.
+  int32_t n_wide = 0, kmax = 0;
+  for (int32_t u = 0; u < shapes.n; ++u) {
+    part[u] = shapes.k[u] > rip::kMaxK;
+    n_wide += part[u];
+    kmax = std::max(kmax, shapes.k[u]);
+  }
+  if (n_wide > 0) {
+    const int64_t all_work = shapes.n * r->tiles[0];
+    if (n_wide < shapes.n &&
+        all_work * rip::policy::wide_plan(kmax, all_work, mom).waves <= rip::policy::kWideAllWaves) {
+      std::memset(part, 1, sizeof part);
+      n_wide = shapes.n;
+    }
+    if (n_wide < shapes.n) {
+      UnitShapes rest;
+      for (int32_t u = 0; u < shapes.n; ++u)
+        if (!part[u]) {
+          rest.k[rest.n] = shapes.k[u];
+          rest.act[rest.n++] = shapes.act[u];
+        }
+      subset_step(a, part, 0, a0);
+      const int cap = rip::policy::launch_waves(rest.k, rest.act, rest.n, mom);
+      if ((rc = launch(a0, 0, cap)) != RIP_OK) return rc;
+    }
+    subset_step(a, part, 1, a1);
+    a1.work = 0;
+    for (int32_t u = 0; u < a1.n_units; ++u) a1.unit_work0[u + 1] = a1.work += (uint32_t)r->tiles[0];
+    const rip::policy::WidePlan plan = rip::policy::wide_plan(kmax, a1.work, mom);
+    for (int32_t u = 0; u < a1.n_units; ++u) {
+      const int k = (int)rip::unit_info_k(a1.unit_info[u]);
+      a1.unit_info[u] = rip::unit_info_pack(rip::unit_info_base(a1.unit_info[u]), (uint32_t)k,
+                                            (uint32_t)rip::policy::wide_share(k, plan.waves));
+    }
+    return launch(a1, plan.waves, plan.per_cu);
+  }
   // One launch, or two when the units want residency caps far apart (and
   // no cap is forced).
-  uint8_t part[RIP_MAX_REPLICAS];
   int w0 = 0, w1 = 0;
   if (forced_bpc == 0 &&
       rip::policy::split_units(shapes.k, shapes.act, shapes.n, mom, part, &w0, &w1)) {
-    rip::StepArgs a0, a1;
     subset_step(a, part, 0, a0);
     subset_step(a, part, 1, a1);
-    if ((rc = launch(a0, w0)) != RIP_OK) return rc;
-    return launch(a1, w1);
+    if ((rc = launch(a0, 0, w0)) != RIP_OK) return rc;
+    return launch(a1, 0, w1);
   }
-  return launch(a, rip::policy::launch_waves(shapes.k, shapes.act, shapes.n, mom));
+  return launch(a, 0, rip::policy::launch_waves(shapes.k, shapes.act, shapes.n, mom));
 }
 
 extern "C" int32_t rip_step(rip_sched* s, const rip_replicas* r, int64_t step,

@@ -14,6 +14,8 @@ namespace rip {
 #endif
 constexpr int kBlock = RIP_BLOCK;  // threads per workgroup: one wave64
 constexpr int kMaxK = 8;           // largest group size with a specialized path
+constexpr int kWideWaves = 16;     // most waves of a workgroup of the wide kernel
+constexpr int kWideC = 4;          // most members a wave of it holds at once
 constexpr int kTileOptions = 4;    // tiles of 1, 2, 4 or 8 slots per thread
 
 // A tile of a unit is kBlock threads x 2^slot_log2(k, mom) slots x 16 bytes
@@ -24,8 +26,8 @@ constexpr int kTileOptions = 4;    // tiles of 1, 2, 4 or 8 slots per thread
 // and the host's residency cap sets the depth of outstanding requests.
 // (A group of three without momentum at one slot streamed 2% faster alone,
 // at 14 waves per CU, but the higher cap it needs slowed the mixed-size
-// launches of Global Division by 1%.)  Groups above kMaxK use one slot and
-// stream their members in chunks of kMaxK.
+// launches of Global Division by 1%.)  Groups above kMaxK use one slot (and
+// the wide kernel).
 constexpr int kSlotLog2Sgd[kMaxK + 1] = {0, 2, 1, 1, 0, 0, 0, 0, 0};
 constexpr int kSlotLog2Mom[kMaxK + 1] = {0, 2, 1, 0, 0, 0, 0, 0, 0};
 constexpr int slot_log2(int k, bool mom) {
@@ -53,12 +55,15 @@ struct StepArgs {
   // The kernel reads the 16 bytes from the dword holding member[base_u], so
   // the table is padded to keep that read inside it.
   alignas(16) uint8_t member[RIP_MAX_REPLICAS + 16];
-  uint32_t active_bits[RIP_MAX_REPLICAS / 32];  // replicas doing their local update
+  // Bit i: replica member[i] does its local update (wide units; read as two
+  // dwords, so one more than the table's).
+  uint32_t member_act[RIP_MAX_REPLICAS / 32 + 1];
 };
 
 // One dword per unit: first member index (8 bits), member count k (9 bits),
 // and the update flags of its first eight members (bit j = member j is
-// active), so a workgroup learns its unit from a single scalar load.
+// active), so a workgroup learns its unit from a single scalar load.  A unit
+// of the wide kernel carries its members per wave in place of the flags.
 constexpr uint32_t unit_info_pack(uint32_t base, uint32_t k, uint32_t act8) {
   return base | (k << 8) | (act8 << 17);
 }
@@ -67,9 +72,13 @@ constexpr uint32_t unit_info_k(uint32_t info) { return (info >> 8) & 0x1FFu; }
 constexpr uint32_t unit_info_act8(uint32_t info) { return info >> 17; }
 static_assert(RIP_MAX_REPLICAS <= 256, "unit_info packs member indices into 8 bits");
 
-// ext: weight decay or Nesterov momentum is on (the kernel variant that
-// handles them; the plain variant leaves them out of the arithmetic).
-hipError_t launch_fused_step(const StepArgs& a, bool bf16, bool mom, bool ext, size_t lds_bytes,
-                             hipStream_t stream);
+// Launches the step's kernel: one wave per workgroup for units of at most
+// kMaxK members (wide_waves 0), or the wide kernel with that many waves per
+// workgroup.  ext: weight decay or Nesterov momentum is on (the kernel variant
+// that handles them; the plain variant leaves them out of the arithmetic).
+// cu_share: bytes of LDS a workgroup takes (0: no cap), which caps how many
+// share a CU.
+hipError_t launch_step(const StepArgs& a, bool bf16, bool mom, bool ext, int wide_waves,
+                       size_t cu_share, hipStream_t stream);
 
 }  // namespace rip

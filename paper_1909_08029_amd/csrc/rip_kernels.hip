@@ -10,10 +10,11 @@
 // per single-wave workgroup, unit after unit.  A tile is 64 lanes x 1-8
 // slots x 16 bytes of each member stream; the slot count shrinks as the
 // unit's number of streams grows (see slot_log2), so every lane keeps 8-16
-// 16-byte loads in flight (24 for a group of eight with momentum).  The host caps residency per launch at 4-14 waves per CU
-// (an LDS reservation), fewer when the units read more streams: HBM3E
-// delivered its best rate at a bounded depth of outstanding requests, not at
-// full occupancy.
+// 16-byte loads in flight (24 for a group of eight with momentum).  The host
+// caps residency per launch at 4-14 waves per CU (an LDS reservation), fewer
+// when the units read more streams: HBM3E delivered its best rate at a bounded
+// depth of outstanding requests, not at full occupancy.  Groups above eight
+// have a kernel of their own (wide_step_kernel).
 // A workgroup handles one unit, so the unit's size k, its member ids and their active
 // flags are wave-uniform: they sit in scalar registers and every branch on
 // them is a scalar branch.  Each thread issues the loads of all members
@@ -42,11 +43,6 @@ namespace rip {
 namespace {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-
-// Replica buffers are plain device memory: the single elements of ragged
-// ends are accessed through the global address space so the compiler emits
-// global_* (not flat_*) instructions.
-#define RIP_GLOBAL __attribute__((address_space(1)))
 
 // Tiles are accessed through buffer instructions, non-temporal (every
 // byte is touched once per step): a descriptor per member stream whose base
@@ -97,11 +93,6 @@ template <typename T>
 __device__ __forceinline__ T cld(const RIP_CONST T* p, int64_t i) {
   return p[i];
 }
-// Byte i of the member table, read as its containing dword.
-__device__ __forceinline__ int cld8(const RIP_CONST uint8_t* p, int i) {
-  const uint32_t word = ((const RIP_CONST uint32_t*)p)[i >> 2];
-  return (int)((word >> ((i & 3) * 8)) & 0xFFu);
-}
 // Bytes i .. i+7 of the (16-byte aligned, padded) member table as one 64-bit
 // value, byte j in bits 8j..8j+7: one 16-byte scalar load of the aligned
 // dwords that hold them, then a funnel shift.
@@ -133,10 +124,6 @@ __device__ __forceinline__ uint32_t bf16_pack2(float lo, float hi) {
   const f32x2 f = {lo, hi};
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2));
 }
-__device__ __forceinline__ uint16_t bf16_round(float f) {
-  return __builtin_bit_cast(uint16_t, (__bf16)f);
-}
-
 template <bool BF16>
 struct Vec;
 
@@ -179,22 +166,6 @@ struct Vec<true> {
     return x;
   }
 };
-
-// Single-element access for ragged ends.
-template <bool BF16>
-__device__ __forceinline__ float ld1(const char* base, int64_t e) {
-  if constexpr (BF16)
-    return __uint_as_float(uint32_t(((const RIP_GLOBAL uint16_t*)base)[e]) << 16);
-  else
-    return ((const RIP_GLOBAL float*)base)[e];
-}
-template <bool BF16>
-__device__ __forceinline__ void st1(char* base, int64_t e, float v) {
-  if constexpr (BF16)
-    ((RIP_GLOBAL uint16_t*)base)[e] = bf16_round(v);
-  else
-    ((RIP_GLOBAL float*)base)[e] = v;
-}
 
 // (float)(1.0/k) for every group size, evaluated at compile time.
 struct InvTable {
@@ -246,6 +217,8 @@ struct Header {
   Opt opt;
 };
 
+__device__ __forceinline__ int lane_id() { return (int)threadIdx.x & (kBlock - 1); }
+
 // The last element of a bf16 tile of odd size: the low half of a dword that
 // the tile's descriptors leave out (so the vector's dword holds 0).  It is in
 // slot e / 64 of lane e % 64, e its vector.
@@ -254,7 +227,7 @@ constexpr int kOutside = 0x7FFFFFF0;  // a byte offset past every tile
 template <int U, typename F>
 __device__ __forceinline__ void odd_load(const char* tile, int bytes, F&& vec) {
   const int at = bytes - 2, e = at >> 4, word = (at >> 2) & 3;
-  const int off = (e & (kBlock - 1)) == (int)threadIdx.x ? at : kOutside;
+  const int off = (e & (kBlock - 1)) == lane_id() ? at : kOutside;
   const uint32_t x = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(tile_rsrc(tile, bytes), off, 0,
                                                                     kNonTemporal);
 #pragma unroll
@@ -265,7 +238,7 @@ __device__ __forceinline__ void odd_load(const char* tile, int bytes, F&& vec) {
 template <int U, typename F>
 __device__ __forceinline__ void odd_store(char* tile, int bytes, F&& vec) {
   const int at = bytes - 2, e = at >> 4, word = (at >> 2) & 3;
-  const int off = (e & (kBlock - 1)) == (int)threadIdx.x ? at : kOutside;
+  const int off = (e & (kBlock - 1)) == lane_id() ? at : kOutside;
   uint32_t x = 0;
 #pragma unroll
   for (int u = 0; u < U; ++u)
@@ -425,144 +398,6 @@ __device__ __forceinline__ void tile_slots(Members& m, int64_t tile_byte, int by
   }
 }
 
-// Element-wise path for the partial tile of a group larger than kMaxK: each
-// thread walks elements e0 + i*stride below `end`.
-template <bool BF16, bool MOM, bool EXT>
-__device__ void elementwise(const Header& h, int base, int k, int seg, int64_t begin,
-                            int64_t end) {
-  const float inv_k = kInv.v[k];
-  const Opt& o = h.opt;
-  for (int64_t e = begin + threadIdx.x; e < end; e += kBlock) {
-    float s = 0.0f;
-    for (int j = 0; j < k; ++j) {
-      const int id = cld8(kargs().member, base + j);
-      const RIP_CONST uint64_t* t = h.ptab + (uint32_t)(seg * h.n_rep + id) * 3u;
-      char* w = reinterpret_cast<char*>(t[0]);
-      float x = ld1<BF16>(w, e);
-      if ((cld(kargs().active_bits, id >> 5) >> (id & 31)) & 1u) {
-        const float g = ld1<BF16>(reinterpret_cast<const char*>(t[1]), e);
-        if constexpr (MOM) {
-          char* vp = reinterpret_cast<char*>(t[2]);
-          float v = ld1<BF16>(vp, e);
-          x = update<true, EXT>(x, g, v, o);
-          st1<BF16>(vp, e, v);
-        } else {
-          float unused = 0.0f;
-          x = update<false, EXT>(x, g, unused, o);
-        }
-      }
-      s = (j == 0) ? x : s + x;
-    }
-    if (k > 1) s = s * inv_k;
-    for (int j = 0; j < k; ++j) {
-      const int id = cld8(kargs().member, base + j);
-      st1<BF16>(reinterpret_cast<char*>(h.ptab[(uint32_t)(seg * h.n_rep + id) * 3u]), e, s);
-    }
-  }
-}
-
-// A full tile of a group larger than kMaxK (All-Reduce as one group of every
-// worker, large divisions): the members stream through in chunks of eight,
-// 16-byte accesses as in tile_slots, their updated values summed into one
-// running fp32 sum in ascending member order; the mean then goes to every
-// member.  Each member's w, g and v are read once and written once, as in
-// the specialized paths; only the member pointers are fetched twice.
-template <bool BF16, bool MOM, bool EXT>
-__device__ __forceinline__ void wide_tile(const Header& h, int base, int k, int seg,
-                                          int64_t e_tile) {
-  using V = Vec<BF16>;
-  constexpr int N = V::N;
-  constexpr int C = kMaxK;  // members per chunk
-  const Opt& o = h.opt;
-  const int64_t tile_byte = e_tile * (BF16 ? 2 : 4);
-  constexpr int kTileBytes = kBlock * 16;
-  const int off = (int)threadIdx.x * 16;
-  float s[N];
-  for (int j0 = 0; j0 < k; j0 += C) {
-    const uint64_t ids = cld8x8(kargs().member, base + j0);  // bytes past the unit are unused
-    char* w[C];
-    const char* g[C];
-    char* v[C];
-    bool act[C];
-#pragma unroll
-    for (int jj = 0; jj < C; ++jj) {
-      const int id = (int)((ids >> (8 * jj)) & 0xFFu);
-      const RIP_CONST uint64_t* e = h.ptab + (uint32_t)(seg * h.n_rep + id) * 3u;
-      const bool in = j0 + jj < k;
-      w[jj] = in ? reinterpret_cast<char*>(e[0]) : nullptr;
-      g[jj] = in ? reinterpret_cast<const char*>(e[1]) : nullptr;
-      v[jj] = in && MOM ? reinterpret_cast<char*>(e[2]) : nullptr;
-      act[jj] = in && ((cld(kargs().active_bits, id >> 5) >> (id & 31)) & 1u);
-    }
-#pragma unroll
-    for (int jj = 0; jj < C; ++jj) {
-      asm volatile("" ::"s"(w[jj]), "s"(g[jj]), "s"((int)act[jj]));
-      if constexpr (MOM) asm volatile("" ::"s"(v[jj]));
-    }
-    Rsrc rw[C], rg[C], rv[C];
-#pragma unroll
-    for (int jj = 0; jj < C; ++jj) {
-      rw[jj] = tile_rsrc(w[jj] + tile_byte, kTileBytes);
-      rg[jj] = tile_rsrc(g[jj] + tile_byte, kTileBytes);
-      if constexpr (MOM) rv[jj] = tile_rsrc(v[jj] + tile_byte, kTileBytes);
-    }
-    u32x4 wv[C], gv[C], vv[C];
-#pragma unroll
-    for (int jj = 0; jj < C; ++jj) {
-      if (j0 + jj < k) {
-        wv[jj] = bld16(rw[jj], off);
-        if (act[jj]) {
-          gv[jj] = bld16(rg[jj], off);
-          if constexpr (MOM) vv[jj] = bld16(rv[jj], off);
-        }
-      }
-    }
-#pragma unroll
-    for (int jj = 0; jj < C; ++jj) {
-      if (j0 + jj < k) {
-        float x[N];
-        V::unpack(wv[jj], x);
-        if (act[jj]) {
-          float gf[N], vf[N];
-          V::unpack(gv[jj], gf);
-          if constexpr (MOM) V::unpack(vv[jj], vf);
-#pragma unroll
-          for (int i = 0; i < N; ++i) x[i] = update<MOM, EXT>(x[i], gf[i], vf[i], o);
-          if constexpr (MOM) vv[jj] = V::pack(vf);
-        }
-#pragma unroll
-        for (int i = 0; i < N; ++i) s[i] = (j0 + jj == 0) ? x[i] : s[i] + x[i];
-      }
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    if constexpr (MOM) {
-#pragma unroll
-      for (int jj = 0; jj < C; ++jj)
-        if (act[jj]) bst16(rv[jj], off, vv[jj]);
-    }
-  }
-  const float inv_k = kInv.v[k];
-#pragma unroll
-  for (int i = 0; i < N; ++i) s[i] = s[i] * inv_k;
-  const u32x4 out = V::pack(s);
-  for (int j0 = 0; j0 < k; j0 += C) {
-    const uint64_t ids = cld8x8(kargs().member, base + j0);
-    char* w[C];
-#pragma unroll
-    for (int jj = 0; jj < C; ++jj) {
-      const int id = (int)((ids >> (8 * jj)) & 0xFFu);
-      w[jj] = j0 + jj < k
-                  ? reinterpret_cast<char*>(h.ptab[(uint32_t)(seg * h.n_rep + id) * 3u])
-                  : nullptr;
-    }
-#pragma unroll
-    for (int jj = 0; jj < C; ++jj) asm volatile("" ::"s"(w[jj]));
-#pragma unroll
-    for (int jj = 0; jj < C; ++jj)
-      if (j0 + jj < k) bst16(tile_rsrc(w[jj] + tile_byte, kTileBytes), off, out);
-  }
-}
-
 // Last index i in [0, n) with v[i] <= x (v ascending, v[0] <= x).
 template <typename P, typename X>
 __device__ __forceinline__ int last_le(P v, int n, X x) {
@@ -581,40 +416,75 @@ struct Unit {
   uint64_t ids;   // member ids 0..7, one per byte
 };
 
-// One tile of a unit of K members (K <= kMaxK, or 0 for the element-wise path
-// with any k).  The tile geometry is a compile-time constant here, so a
+__device__ __forceinline__ Header load_header(KArgs* a) {
+  // Load the whole header into scalar registers in one batch up front: left
+  // to itself the compiler spreads it over several batches (and loads
+  // flat_numel late, through a select of addresses), and every extra batch is
+  // one more dependent scalar round trip before the workgroup's first vector
+  // load.
+  const Header h{(const RIP_CONST uint64_t*)a->ptab, (const RIP_CONST int64_t*)a->seg_numel,
+                 (const RIP_CONST int64_t*)a->seg_tile0, a->work, a->blocks, a->uniform_k, a->n_seg,
+                 a->n_rep, a->n_units, a->flat_numel,
+                 Opt{a->lr, a->mu, a->wd, a->nesterov != 0}};
+  asm volatile("" ::"s"(h.ptab), "s"(h.seg_numel), "s"(h.seg_tile0), "s"(h.work), "s"(h.blocks), "s"(h.uniform_k), "s"(h.n_seg),
+               "s"(h.n_rep), "s"(h.n_units), "s"(h.flat_numel), "s"(h.opt.lr), "s"(h.opt.mu),
+               "s"(h.opt.wd), "s"((int)h.opt.nesterov));
+  return h;
+}
+
+// The unit and tile of work item w.  A launch of units with the same tile
+// count has a grid of one row per unit; otherwise the grid is one row of work
+// items, unit after unit.
+__device__ __forceinline__ int find_unit(KArgs* a, const Header& h, uint32_t w, int64_t& tile) {
+  if (h.blocks == 0) {
+    tile = (int64_t)w;
+    return (int)blockIdx.y;
+  }
+  const int unit = last_le(a->unit_work0, h.n_units, w);
+  tile = (int64_t)(w - cld(a->unit_work0, unit));
+  return unit;
+}
+
+// Where a tile lies: its segment, first element and element count.
+struct Place {
+  int seg, elems;
+  int64_t e_tile;
+};
+
+// The place of tile `tile` of a unit, for tiles of TE elements (slot option
+// O).  A flat handle needs no search.
+template <int64_t TE>
+__device__ __forceinline__ Place find_place(const Header& h, int O, int64_t tile) {
+  Place p;
+  int64_t numel;
+  if (h.n_seg == 1) {
+    p.seg = 0;
+    p.e_tile = tile * TE;
+    numel = h.flat_numel;
+  } else {
+    const RIP_CONST int64_t* tile0 = h.seg_tile0 + O * (h.n_seg + 1);
+    p.seg = last_le(tile0, h.n_seg, tile);
+    p.e_tile = (tile - cld(tile0, p.seg)) * TE;
+    numel = cld(h.seg_numel, p.seg);
+  }
+  p.elems = (int)(p.e_tile + TE <= numel ? TE : numel - p.e_tile);
+  return p;
+}
+
+// One tile of a unit of K members.  The tile geometry is a compile-time constant here, so a
 // workgroup reaches its first vector load after a handful of scalar
 // instructions: a flat handle needs no segment search at all.
 template <int K, bool BF16, bool MOM, bool EXT>
 __device__ __forceinline__ void unit_tile(const Header& h, const Unit& u, int64_t tile) {
-  constexpr int O = slot_log2(K == 0 ? kMaxK + 1 : K, MOM);
+  constexpr int O = slot_log2(K, MOM);
   constexpr int SL = 1 << O;
   constexpr int N = Vec<BF16>::N;
   constexpr int64_t TE = (int64_t)kBlock * N * SL;  // elements per tile
-  int seg = 0;
-  int64_t e_tile, numel;
-  if (h.n_seg == 1) {
-    e_tile = tile * TE;
-    numel = h.flat_numel;
-  } else {
-    const RIP_CONST int64_t* tile0 = h.seg_tile0 + O * (h.n_seg + 1);
-    seg = last_le(tile0, h.n_seg, tile);
-    e_tile = (tile - cld(tile0, seg)) * TE;
-    numel = cld(h.seg_numel, seg);
-  }
-  if constexpr (K > 0) {
-    constexpr int esize = BF16 ? 2 : 4;
-    Members m;
-    load_members<K, MOM>(h, u.ids, u.act8, seg, m);
-    const int bytes = (int)(e_tile + TE <= numel ? TE : numel - e_tile) * esize;
-    tile_slots<K, SL, BF16, MOM, EXT>(m, e_tile * esize, bytes, h.opt);
-  } else {
-    if (e_tile + TE <= numel) {
-      wide_tile<BF16, MOM, EXT>(h, u.base, u.k, seg, e_tile);
-      return;
-    }
-    elementwise<BF16, MOM, EXT>(h, u.base, u.k, seg, e_tile, numel);
-  }
+  const Place at = find_place<TE>(h, O, tile);
+  constexpr int esize = BF16 ? 2 : 4;
+  Members m;
+  load_members<K, MOM>(h, u.ids, u.act8, at.seg, m);
+  tile_slots<K, SL, BF16, MOM, EXT>(m, at.e_tile * esize, at.elems * esize, h.opt);
 }
 
 template <bool BF16, bool MOM, bool EXT>
@@ -629,29 +499,9 @@ __global__ __launch_bounds__(kBlock) void fused_step_kernel(StepArgs) {
     // a launch, now 1.93, of which an empty kernel takes 1.65).
     KArgs* a = &kargs();
     asm volatile("" : "+s"(a));
-    // Load the whole header into scalar registers in one batch up front: left
-    // to itself the compiler spreads it over several batches (and loads
-    // flat_numel late, through a select of addresses), and every extra batch is
-    // one more dependent scalar round trip before the workgroup's first vector
-    // load.
-    const Header h{(const RIP_CONST uint64_t*)a->ptab, (const RIP_CONST int64_t*)a->seg_numel,
-                   (const RIP_CONST int64_t*)a->seg_tile0, a->work, a->blocks, a->uniform_k, a->n_seg,
-                   a->n_rep, a->n_units, a->flat_numel,
-                   Opt{a->lr, a->mu, a->wd, a->nesterov != 0}};
-    asm volatile("" ::"s"(h.ptab), "s"(h.seg_numel), "s"(h.seg_tile0), "s"(h.work), "s"(h.blocks), "s"(h.uniform_k), "s"(h.n_seg),
-                 "s"(h.n_rep), "s"(h.n_units), "s"(h.flat_numel), "s"(h.opt.lr), "s"(h.opt.mu),
-                 "s"(h.opt.wd), "s"((int)h.opt.nesterov));
-    // A launch of units with the same tile count has a grid of one row per
-    // unit; otherwise the grid is one row of work items, unit after unit.
-    int unit;
+    const Header h = load_header(a);
     int64_t tile;
-    if (h.blocks == 0) {
-      unit = (int)blockIdx.y;
-      tile = (int64_t)w;
-    } else {
-      unit = last_le(a->unit_work0, h.n_units, w);
-      tile = (int64_t)(w - cld(a->unit_work0, unit));
-    }
+    const int unit = find_unit(a, h, w, tile);
     // With equal-sized units the member window's address needs no load, so
     // it is fetched together with the unit's info word: the unit costs one
     // scalar round trip, its members' pointers a second.
@@ -674,8 +524,7 @@ __global__ __launch_bounds__(kBlock) void fused_step_kernel(StepArgs) {
       case 5: unit_tile<5, BF16, MOM, EXT>(h, u, tile); break;
       case 6: unit_tile<6, BF16, MOM, EXT>(h, u, tile); break;
       case 7: unit_tile<7, BF16, MOM, EXT>(h, u, tile); break;
-      case 8: unit_tile<8, BF16, MOM, EXT>(h, u, tile); break;
-      default: unit_tile<0, BF16, MOM, EXT>(h, u, tile); break;
+      default: unit_tile<8, BF16, MOM, EXT>(h, u, tile); break;
     }
     if (h.blocks == 0) return;
     w += h.blocks;
@@ -683,26 +532,230 @@ __global__ __launch_bounds__(kBlock) void fused_step_kernel(StepArgs) {
   }
 }
 
+// Groups larger than kMaxK (All-Reduce as one group of every worker, large
+// divisions): one workgroup per tile (one 16-byte slot per lane), its waves
+// sharing the members.  A wave holds c <= kWideC members, issues all their
+// loads together and updates them; the sum then passes from wave to wave
+// through LDS, so it is still taken in ascending member order, and the wave
+// with the last members hands the mean to all.  A group of more members than
+// the waves hold goes in rounds; a wave loads its next members while the sum
+// is with the others.
+//
+// Bound by the latency of a workgroup where a launch is small, and by the
+// number of streams open at once where it is large.  Single waves that took
+// the members in chunks of eight one after the other waited for every chunk's
+// loads by themselves and left most of the chip idle on small replicas: 256
+// bf16 replicas of 65,539 93.2 us, now 32.0; 64 fp32 of 10,000 21.8, now 7.0;
+// 9 fp32 of 4M 85.1, now 70.2; 32 fp32 of 25.6M 1757, now 1702 (5.8 TB/s);
+// groups of 12 to 16 of 8M and more are between 5% faster and 3% slower.  Four
+// members a wave: with eight, the updated values of a bf16 wave take 150-185
+// VGPRs, and one workgroup fits a CU (64 bf16 of 2.5M 221 us, now 176); two or
+// four slots per lane helped only at one size in ten.
+//
+// Each turn waits for the one before it only, on a counter in LDS that the
+// wave holding the sum advances; every turn belongs to a wave of the same
+// workgroup, which takes its turns in ascending order, so every wait ends.
+constexpr uint32_t kWideDone = ~0u;  // the turn counter once the mean is there
+struct WideShared {
+  float sum[8][kBlock];  // [element of the lane's vector][lane]
+  u32x4 mean[kBlock];
+  uint32_t turn;
+};
+
+__device__ __forceinline__ void wait_turn(uint32_t* turn, uint32_t t) {
+  while ((uint32_t)__builtin_amdgcn_readfirstlane(
+             (int)__hip_atomic_load(turn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) != t) {
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+__device__ __forceinline__ void pass_turn(uint32_t* turn, uint32_t t) {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __hip_atomic_store(turn, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// Pointers of the members at base .. base + kWideC - 1 of the member table, to
+// the tile (all of them, or only the parameters; the table's entries past the
+// unit belong to the next one or are 0, and are not used).
+template <bool ALL, bool MOM>
+__device__ __forceinline__ void wide_members(KArgs* a, const Header& h, int base, int seg,
+                                             int64_t tile_byte, Members& m) {
+  const uint64_t ids = cld8x8(a->member, base);
+#pragma unroll
+  for (int j = 0; j < kWideC; ++j) {
+    const int id = (int)((ids >> (8 * j)) & 0xFFu);
+    const RIP_CONST uint64_t* e = h.ptab + (uint32_t)(seg * h.n_rep + id) * 3u;
+    m.w[j] = reinterpret_cast<char*>(e[0]) + tile_byte;
+    if constexpr (ALL) {
+      m.g[j] = reinterpret_cast<const char*>(e[1]) + tile_byte;
+      if constexpr (MOM) m.v[j] = reinterpret_cast<char*>(e[2]) + tile_byte;
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < kWideC; ++j) {
+    asm volatile("" ::"s"(m.w[j]));
+    if constexpr (ALL) {
+      asm volatile("" ::"s"(m.g[j]));
+      if constexpr (MOM) asm volatile("" ::"s"(m.v[j]));
+    }
+  }
+}
+
+template <bool BF16, bool MOM, bool EXT>
+__global__ __launch_bounds__(kBlock * kWideWaves) void wide_step_kernel(StepArgs) {
+  using V = Vec<BF16>;
+  constexpr int N = V::N;
+  constexpr int64_t TE = (int64_t)kBlock * N;
+  constexpr int esize = BF16 ? 2 : 4;
+  __shared__ WideShared sh;
+  const int lane = lane_id();
+  const int off = lane * 16;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kBlock);
+  uint32_t w = blockIdx.x;
+  for (;;) {
+    if (threadIdx.x == 0) sh.turn = 0;
+    __syncthreads();
+    KArgs* a = &kargs();
+    asm volatile("" : "+s"(a));
+    const Header h = load_header(a);
+    int64_t tile;
+    const int unit = find_unit(a, h, w, tile);
+    const uint32_t info = cld(a->unit_info, unit);
+    const int k = (int)unit_info_k(info), base = (int)unit_info_base(info);
+    const int c = (int)unit_info_act8(info);  // members per wave and round
+    const Place at = find_place<TE>(h, 0, tile);
+    const int64_t tile_byte = at.e_tile * esize;
+    const int bytes = at.elems * esize;
+    const bool odd = BF16 && (bytes & 2);
+    const int per_round = c * (int)(blockDim.x / kBlock);
+    Members m;
+    for (int j0 = wave * c; j0 < k; j0 += per_round) {
+      const int n = k - j0 < c ? k - j0 : c;
+      wide_members<true, MOM>(a, h, base + j0, at.seg, tile_byte, m);
+      // the members' flags: bits base + j0 .. of the position-ordered mask
+      const int bit = base + j0;
+      const uint64_t two = cld(a->member_act, bit >> 5) |
+                           ((uint64_t)cld(a->member_act, (bit >> 5) + 1) << 32);
+      m.act = (uint32_t)(two >> (bit & 31)) & ((1u << n) - 1u);
+      u32x4 wv[kWideC], gv[kWideC], vv[kWideC];
+#pragma unroll
+      for (int j = 0; j < kWideC; ++j) {
+        if (j < n) wv[j] = bld16(tile_rsrc(m.w[j], bytes & ~3), off);
+        if (m.active(j)) {
+          gv[j] = bld16(tile_rsrc(m.g[j], bytes & ~3), off);
+          if constexpr (MOM) vv[j] = bld16(tile_rsrc(m.v[j], bytes & ~3), off);
+        }
+      }
+      if constexpr (BF16) {
+        if (__builtin_expect(odd, 0)) {
+#pragma unroll
+          for (int j = 0; j < kWideC; ++j) {
+            if (j < n) odd_load<1>(m.w[j], bytes, [&](int) -> u32x4& { return wv[j]; });
+            if (m.active(j)) {
+              odd_load<1>(m.g[j], bytes, [&](int) -> u32x4& { return gv[j]; });
+              if constexpr (MOM) odd_load<1>(m.v[j], bytes, [&](int) -> u32x4& { return vv[j]; });
+            }
+          }
+        }
+      }
+      asm volatile("" : "+s"(m.act));
+      float x[kWideC][N];
+#pragma unroll
+      for (int j = 0; j < kWideC; ++j) {
+        if (j < n) V::unpack(wv[j], x[j]);
+        if (m.active(j)) {
+          float g[N], v[N];
+          V::unpack(gv[j], g);
+          if constexpr (MOM) V::unpack(vv[j], v);
+#pragma unroll
+          for (int i = 0; i < N; ++i) x[j][i] = update<MOM, EXT>(x[j][i], g[i], v[i], h.opt);
+          if constexpr (MOM) vv[j] = V::pack(v);
+        }
+        __builtin_amdgcn_sched_barrier(0);  // one member at a time: fewer registers
+      }
+      if constexpr (MOM) {
+        asm volatile("" : "+s"(m.act));
+#pragma unroll
+        for (int j = 0; j < kWideC; ++j)
+          if (m.active(j)) {
+            bst16(tile_rsrc(m.v[j], bytes & ~3), off, vv[j]);
+            if (odd) odd_store<1>(m.v[j], bytes, [&](int) { return vv[j]; });
+          }
+      }
+      // The sum, from the wave that holds the members before these.
+      const uint32_t turn = (uint32_t)(j0 / c);
+      float s[N];
+      if (turn > 0) {
+        wait_turn(&sh.turn, turn);
+#pragma unroll
+        for (int i = 0; i < N; ++i) s[i] = sh.sum[i][lane] + x[0][i];
+      } else {
+#pragma unroll
+        for (int i = 0; i < N; ++i) s[i] = x[0][i];
+      }
+#pragma unroll
+      for (int j = 1; j < kWideC; ++j)
+        if (j < n) {
+#pragma unroll
+          for (int i = 0; i < N; ++i) s[i] = s[i] + x[j][i];
+        }
+      if (j0 + n < k) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) sh.sum[i][lane] = s[i];
+        pass_turn(&sh.turn, turn + 1);
+      } else {
+        const float inv_k = kInv.v[k];
+#pragma unroll
+        for (int i = 0; i < N; ++i) s[i] = s[i] * inv_k;
+        sh.mean[lane] = V::pack(s);
+        pass_turn(&sh.turn, kWideDone);
+      }
+    }
+    wait_turn(&sh.turn, kWideDone);
+    const u32x4 out = sh.mean[lane];
+    for (int j0 = wave * c; j0 < k; j0 += per_round) {
+      const int n = k - j0 < c ? k - j0 : c;
+      wide_members<false, MOM>(a, h, base + j0, at.seg, tile_byte, m);
+#pragma unroll
+      for (int j = 0; j < kWideC; ++j)
+        if (j < n) {
+          bst16(tile_rsrc(m.w[j], bytes & ~3), off, out);
+          if (odd) odd_store<1>(m.w[j], bytes, [&](int) { return out; });
+        }
+    }
+    if (h.blocks == 0) return;
+    w += h.blocks;
+    if (w >= h.work) return;
+    __syncthreads();
+  }
+}
+
 }  // namespace
 
 namespace {
 template <bool BF16, bool MOM>
-const void* kernel_for(bool ext) {
+const void* kernel_for(bool ext, bool wide) {
+  if (wide)
+    return ext ? reinterpret_cast<const void*>(&wide_step_kernel<BF16, MOM, true>)
+               : reinterpret_cast<const void*>(&wide_step_kernel<BF16, MOM, false>);
   return ext ? reinterpret_cast<const void*>(&fused_step_kernel<BF16, MOM, true>)
              : reinterpret_cast<const void*>(&fused_step_kernel<BF16, MOM, false>);
 }
 }  // namespace
 
-hipError_t launch_fused_step(const StepArgs& a, bool bf16, bool mom, bool ext, size_t lds_bytes,
-                             hipStream_t stream) {
-  const void* fn = bf16 ? (mom ? kernel_for<true, true>(ext) : kernel_for<true, false>(ext))
-                        : (mom ? kernel_for<false, true>(ext) : kernel_for<false, false>(ext));
+hipError_t launch_step(const StepArgs& a, bool bf16, bool mom, bool ext, int wide_waves,
+                       size_t cu_share, hipStream_t stream) {
+  const bool wide = wide_waves > 0;
+  const void* fn = bf16 ? (mom ? kernel_for<true, true>(ext, wide) : kernel_for<true, false>(ext, wide))
+                        : (mom ? kernel_for<false, true>(ext, wide)
+                               : kernel_for<false, false>(ext, wide));
   void* args[] = {const_cast<StepArgs*>(&a)};
-  // hipLaunchKernel reports this launch's own status (not an earlier sticky error).
-  // lds_bytes is a reservation only (the kernel uses no LDS): it caps how
-  // many workgroups share a CU.
   const dim3 grid = a.blocks ? dim3(a.blocks) : dim3(a.work / a.n_units, a.n_units);
-  return hipLaunchKernel(fn, grid, dim3(kBlock), args, lds_bytes, stream);
+  // The dynamic LDS is a reservation only: it caps how many workgroups share
+  // a CU.
+  const size_t own = wide ? sizeof(WideShared) : 0;
+  const size_t lds = cu_share > own ? cu_share - own : 0;
+  // hipLaunchKernel reports this launch's own status (not an earlier sticky error).
+  return hipLaunchKernel(fn, grid, dim3(wide ? kBlock * wide_waves : kBlock), args, lds, stream);
 }
 
 }  // namespace rip

@@ -12,8 +12,8 @@ namespace policy {
 constexpr int kMaxK = 8;  // largest group size with a specialized kernel path
 
 // Resident waves per CU at which each unit shape sustained the most HBM
-// bandwidth on MI355X, by group size k (entry 0: groups above kMaxK, which
-// stream their members in chunks of kMaxK), for units whose members all
+// bandwidth on MI355X, by group size k (entry 0: groups above kMaxK streamed
+// by single waves; their kernel takes wide_plan below instead), for units whose members all
 // update (plain SGD, momentum) and for units that only average.  Measured
 // with bench.py --sweep-caps (32 fp32 replicas of 25.6M parameters, every
 // unit of one size, even caps of 2-16 waves/CU, one process per shape; two
@@ -60,6 +60,49 @@ inline int launch_waves(const int32_t* k, const int32_t* act, int32_t units, boo
   }
   if (den == 0.0) return kWavesDefault;
   return 2 * (int)std::ceil(num / den / 2.0 - 1e-6);
+}
+
+// The wide kernel's launch (units above kMaxK members): waves per workgroup
+// and workgroups per CU.
+constexpr int kWideWaves = 16;  // most waves of a workgroup
+constexpr int kWideC = 4;       // most members a wave holds at once
+constexpr int kCus = 256;       // compute units of an MI355X
+// Most waves of a wide launch that also takes a step's smaller units, most of
+// whose waves have no member (a second launch costs about 2 us; a group of 16
+// beside a lone update of 300,077, 9.4k waves: 11.2 us, 13.7 as two launches;
+// 32 beside 8 of 80,077 with momentum, 22k waves: 18.0, 15.2 as two).
+constexpr int kWideAllWaves = 10240;
+
+struct WidePlan {
+  int waves, per_cu;
+};
+
+// Four members per wave as far as the waves go: eight waves, or sixteen when
+// every workgroup has a CU to itself, where only the latency of a workgroup
+// counts (256 bf16 replicas of 65,539: 28.8 us with sixteen, 38.4 with eight),
+// or with momentum (64 fp32 replicas of 4M: 953 us, 985 with eight; with plain
+// SGD, 64 of 600,077: 94.7, with eight 90.6).  Sixteen waves share a CU (fp32
+// groups of 16, 10M: 325 us at 16, 342 at 12, 338 at 20-24), more when that
+// lets all workgroups start at once (24 fp32 replicas of 150,077: 7.3 us with
+// four workgroups of six waves a CU, 9.7 with two).  Workgroups per CU are
+// even (an odd count gets the residency of the even one below).
+inline WidePlan wide_plan(int32_t kmax, int64_t work, bool mom) {
+  WidePlan p;
+  const int most = mom || work <= kCus ? kWideWaves : kWideWaves / 2;
+  p.waves = (kmax + kWideC - 1) / kWideC;
+  if (p.waves > most) p.waves = most;
+  const auto even = [](int64_t n) { return n < 2 ? n : (n + 1) / 2 * 2; };
+  p.per_cu = (int)(p.waves == 3 ? 4 : even(16 / p.waves));
+  const int64_t all = even((work + kCus - 1) / kCus);
+  if (all > p.per_cu && all * p.waves <= 32) p.per_cu = (int)all;
+  return p;
+}
+
+// Members per wave and round of a unit of k members on `waves` waves: the
+// rounds' members split evenly.
+inline int wide_share(int32_t k, int waves) {
+  const int rounds = (k + kWideC * waves - 1) / (kWideC * waves);
+  return (k + rounds * waves - 1) / (rounds * waves);
 }
 
 // A step whose units prefer caps far apart (Global Division and Inter-Intra

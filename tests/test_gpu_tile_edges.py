@@ -62,7 +62,7 @@ def _check(bf16, mom, k, sizes, average=False, wd=0.0, nesterov=False, lone=1):
     import torch
     import paper_1909_08029_amd as rip
     rng = np.random.default_rng(1000 * k + sum(sizes))
-    n = k + lone + 1                       # one replica is left alone
+    n = k + lone + 1                       # the last replica is left alone
     p, g, v = (_arrays(rng, n, sizes, bf16) for _ in range(3))
     P, G, V = Guarded(p), Guarded(g), Guarded(v)
     rep = rip.Replicas(P.views, G.views, V.views)
@@ -98,3 +98,31 @@ def test_segment_ends(bf16, mom, k):
     _check(bf16, mom, k, [64 * N + 3], wd=1e-2, nesterov=mom)
     if k > 1:
         _check(bf16, False, k, [64 * N + 3, 7], average=True)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("mom", [False, True])
+@pytest.mark.parametrize("k", [9, 16, 17, 31, 33, 64, 65, 127, 130, 254])
+def test_wide_groups(bf16, mom, k):
+    """Groups above eight: their members are shared by the waves of a
+    workgroup, evenly and in rounds.  A lone replica beside the group runs in
+    the same launch while that is small, in one of its own above."""
+    import paper_1909_08029_amd as rip
+    N = 8 if bf16 else 4
+    log(f"case wide bf16={bf16} mom={mom} k={k}")
+    for m in (1, N, N + 1, 64 * N - 1, 64 * N, 64 * N + N + 3, 3 * 64 * N + 63 * N + 1):
+        _check(bf16, mom, k, [m], lone=k % 2)
+        assert rip.rip_last_launch_count() == 1
+    _check(bf16, mom, k, [5, 64 * N + 1, 1, 64 * N], lone=0)
+    _check(bf16, mom, k, [64 * N + 3], wd=1e-2, nesterov=mom, lone=0)
+    _check(bf16, False, k, [64 * N + 3, 7], average=True, lone=0)
+    try:                                   # workgroups that loop over tiles, one per CU
+        rip.rip_set_max_blocks(3)
+        rip.rip_set_blocks_per_cu(1)
+        _check(bf16, mom, k, [64 * N * 11 + N + 1, 64 * N], lone=0)
+    finally:
+        rip.rip_set_max_blocks(0)
+        rip.rip_set_blocks_per_cu(0)
+    if k < 20:
+        _check(bf16, mom, k, [64 * N * 1800 + 3], lone=1)
+        assert rip.rip_last_launch_count() == 2
