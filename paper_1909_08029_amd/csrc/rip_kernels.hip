@@ -375,17 +375,34 @@ __device__ __forceinline__ void tile_slots(Members& m, int64_t tile_byte, int by
   // Keep the instruction scheduler from sinking arithmetic below the stores.
   __builtin_amdgcn_sched_barrier(0);
   asm volatile("" : "+s"(m.act));
+  // A wave of a large group with momentum has 12-16 stores, and issued back
+  // to back they cost the HBM3E rate: 16 cycles between them gave 16 fp32
+  // replicas of 138.4M (groups of eight) 7462 -> 7395 us, groups of six of
+  // 25.6M 1519 -> 1511; with fewer streams the pause itself costs (groups of
+  // eight without momentum -2%, lone updates with it -2%).
+  const auto pace = [] {
+    if constexpr (MOM && K >= 6) {
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("s_nop 15");
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
   if constexpr (MOM) {
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int j = 0; j < K; ++j)
+      for (int j = 0; j < K; ++j) {
         if (m.active(j)) bst16(tile_rsrc(m.v[j], bytes & ~3), off[u], vv[u][j]);
+        pace();
+      }
   }
 #pragma unroll
   for (int u = 0; u < U; ++u)
 #pragma unroll
-    for (int j = 0; j < K; ++j) bst16(tile_rsrc(m.w[j], bytes & ~3), off[u], out[u]);
+    for (int j = 0; j < K; ++j) {
+      bst16(tile_rsrc(m.w[j], bytes & ~3), off[u], out[u]);
+      pace();
+    }
   if constexpr (BF16) {
     if (__builtin_expect(odd, 0)) {
 #pragma unroll
