@@ -502,9 +502,10 @@ int32_t build_step(const rip_replicas* r, const int32_t* group_offsets, const in
   mom = sgd && sgd->momentum != 0.0f && n_active > 0;
   int64_t work = 0;
   a.unit_work0[0] = 0;
+  a.one_slot = units * r->tiles[0] <= rip::policy::kOneSlotWork;
   for (int32_t u = 0; u < units; ++u) {
     const int k = unit_off[u + 1] - unit_off[u];
-    work += r->tiles[rip::slot_log2(k, mom)];
+    work += r->tiles[a.one_slot ? 0 : rip::slot_log2(k, mom)];
     if (work >= (int64_t)1 << 31)
       return rip::fail(RIP_E_UNSUPPORTED, "more than 2^31 tiles in one step (replicas too large)");
     a.unit_work0[u + 1] = (uint32_t)work;

@@ -46,6 +46,7 @@ struct StepArgs {
   uint32_t blocks;            // workgroups of a one-row grid; 0: the grid has one row of
                               // work / n_units workgroups per unit (equal tile counts)
   uint32_t uniform_k;         // members per unit when all units have the same size, else 0
+  int32_t one_slot;           // nonzero: every tile is one slot, whatever the unit
   int64_t flat_numel;         // elements of the only segment when n_seg == 1
   float lr, mu, wd;
   int32_t nesterov;

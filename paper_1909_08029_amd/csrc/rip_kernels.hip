@@ -212,7 +212,7 @@ struct Header {
   const RIP_CONST uint64_t* ptab;
   const RIP_CONST int64_t *seg_numel, *seg_tile0;
   uint32_t work, blocks, uniform_k;
-  int n_seg, n_rep, n_units;
+  int n_seg, n_rep, n_units, one_slot;
   int64_t flat_numel;
   Opt opt;
 };
@@ -441,10 +441,10 @@ __device__ __forceinline__ Header load_header(KArgs* a) {
   // load.
   const Header h{(const RIP_CONST uint64_t*)a->ptab, (const RIP_CONST int64_t*)a->seg_numel,
                  (const RIP_CONST int64_t*)a->seg_tile0, a->work, a->blocks, a->uniform_k, a->n_seg,
-                 a->n_rep, a->n_units, a->flat_numel,
+                 a->n_rep, a->n_units, a->one_slot, a->flat_numel,
                  Opt{a->lr, a->mu, a->wd, a->nesterov != 0}};
   asm volatile("" ::"s"(h.ptab), "s"(h.seg_numel), "s"(h.seg_tile0), "s"(h.work), "s"(h.blocks), "s"(h.uniform_k), "s"(h.n_seg),
-               "s"(h.n_rep), "s"(h.n_units), "s"(h.flat_numel), "s"(h.opt.lr), "s"(h.opt.mu),
+               "s"(h.n_rep), "s"(h.n_units), "s"(h.one_slot), "s"(h.flat_numel), "s"(h.opt.lr), "s"(h.opt.mu),
                "s"(h.opt.wd), "s"((int)h.opt.nesterov));
   return h;
 }
@@ -491,9 +491,8 @@ __device__ __forceinline__ Place find_place(const Header& h, int O, int64_t tile
 // One tile of a unit of K members.  The tile geometry is a compile-time constant here, so a
 // workgroup reaches its first vector load after a handful of scalar
 // instructions: a flat handle needs no segment search at all.
-template <int K, bool BF16, bool MOM, bool EXT>
-__device__ __forceinline__ void unit_tile(const Header& h, const Unit& u, int64_t tile) {
-  constexpr int O = slot_log2(K, MOM);
+template <int K, int O, bool BF16, bool MOM, bool EXT>
+__device__ __forceinline__ void tile_of(const Header& h, const Unit& u, int64_t tile) {
   constexpr int SL = 1 << O;
   constexpr int N = Vec<BF16>::N;
   constexpr int64_t TE = (int64_t)kBlock * N * SL;  // elements per tile
@@ -502,6 +501,17 @@ __device__ __forceinline__ void unit_tile(const Header& h, const Unit& u, int64_
   Members m;
   load_members<K, MOM>(h, u.ids, u.act8, at.seg, m);
   tile_slots<K, SL, BF16, MOM, EXT>(m, at.e_tile * esize, at.elems * esize, h.opt);
+}
+template <int K, bool BF16, bool MOM, bool EXT>
+__device__ __forceinline__ void unit_tile(const Header& h, const Unit& u, int64_t tile) {
+  constexpr int O = slot_log2(K, MOM);
+  if constexpr (O > 0) {
+    if (h.one_slot) {
+      tile_of<K, 0, BF16, MOM, EXT>(h, u, tile);
+      return;
+    }
+  }
+  tile_of<K, O, BF16, MOM, EXT>(h, u, tile);
 }
 
 template <bool BF16, bool MOM, bool EXT>

@@ -62,6 +62,14 @@ inline int launch_waves(const int32_t* k, const int32_t* act, int32_t units, boo
   return 2 * (int)std::ceil(num / den / 2.0 - 1e-6);
 }
 
+// A launch of at most this many one-slot tiles (four waves per CU) takes
+// one-slot tiles for every unit: more waves, each with fewer loads and less
+// code to fetch, finish sooner while the chip is not full.  (8 fp32 replicas
+// of 10,007 in pairs: 2.5 us with two slots, 2.0 with one; with momentum 3.0
+// and 2.2; lone bf16 updates with momentum 3.1 with four slots, 2.3 with one.
+// Pairs of 80,007, 1252 tiles: 3.5 and 3.8; of 160,007, 2500 tiles: 4.4, 5.1.)
+constexpr int kOneSlotWork = 1024;
+
 // The wide kernel's launch (units above kMaxK members): waves per workgroup
 // and workgroups per CU.
 constexpr int kWideWaves = 16;  // most waves of a workgroup
