@@ -13,11 +13,16 @@ constexpr int kMaxK = 8;  // largest group size with a specialized kernel path
 
 // Resident waves per CU at which each unit shape sustained the most HBM
 // bandwidth on MI355X, by group size k (entry 0: groups above kMaxK streamed
-// by single waves; their kernel takes wide_plan below instead), for units whose members all
-// update (plain SGD, momentum) and for units that only average.  Measured
-// with bench.py --sweep-caps (32 fp32 replicas of 25.6M parameters, every
-// unit of one size, even caps of 2-16 waves/CU, one process per shape; two
-// sessions on different machines agreed).  A lane keeps one 16-byte load in
+// by single waves; their kernel takes wide_plan below instead), for units
+// whose members all update (plain SGD, momentum) and for units that only
+// average.  Measured with bench.py --sweep-caps (32 fp32 replicas of 25.6M
+// parameters, every unit of one size, even caps of 2-16 waves/CU, one process
+// per shape; two sessions on different machines agreed) and again in replayed
+// graphs on 14-16 replicas of 16.8M.  With the kernel's shorter way to a
+// wave's first load some shapes peak two waves lower than before (replicas of
+// 25.6M, before -> after: lone updates 781 -> 773 us at 12 -> 10, groups of
+// seven 1380 -> 1333 at 8 -> 6, with momentum 1747 -> 1716 and groups of six
+// 1475 -> 1464 at 6 -> 4; averaging only, triples 583 -> 572 at 10 -> 8).  A lane keeps one 16-byte load in
 // flight per slot of every stream it reads (w, plus g and v when the member
 // updates), so units that read more streams peak with fewer resident waves;
 // beyond that, more waves add outstanding requests without adding bandwidth
@@ -29,9 +34,9 @@ constexpr int kMaxK = 8;  // largest group size with a specialized kernel path
 // CU's LDS), so only even caps are used.  bf16 units (8 replicas of 1.3G
 // parameters) peaked at the same caps within 2%, except averaging-only groups
 // of eight, which ran 5% faster at 6 than at 8 (fp32: equal).
-constexpr int kWavesSgd[kMaxK + 1] = {4, 12, 10, 8, 10, 8, 8, 8, 6};
-constexpr int kWavesMom[kMaxK + 1] = {4, 12, 10, 10, 8, 6, 6, 6, 4};
-constexpr int kWavesAvg[kMaxK + 1] = {6, 12, 14, 10, 12, 10, 8, 8, 6};
+constexpr int kWavesSgd[kMaxK + 1] = {4, 10, 10, 8, 10, 8, 8, 6, 6};
+constexpr int kWavesMom[kMaxK + 1] = {4, 10, 10, 10, 8, 6, 4, 4, 4};
+constexpr int kWavesAvg[kMaxK + 1] = {6, 12, 12, 8, 12, 10, 8, 6, 6};
 
 // The cap used when a launch has no units (nothing is launched then).
 constexpr int kWavesDefault = 8;
