@@ -158,7 +158,7 @@ def _i32_call(values):
 def _csr_call(groups):
     offsets, members = [0], []
     for g in groups:
-        members += g
+        members.extend(g)
         offsets.append(len(members))
     try:
         m = array.array("i", members)
