@@ -581,6 +581,8 @@ extern "C" int32_t rip_preduce(const rip_replicas* r, const int32_t* group_offse
   auto launch = [&](rip::StepArgs& x, int wide_waves, int per_cu) -> int32_t {
     if (x.work == 0) return RIP_OK;
     set_grid(x, (uint32_t)max_blocks);
+    if (wide_waves == 0)
+      per_cu = rip::policy::short_cap(per_cu, x.work, mom && r->dtype == RIP_BF16);
     const int bpc = forced_bpc > 0 ? forced_bpc : per_cu;
     const size_t share = r->lds_per_cu > 0 ? (size_t)(r->lds_per_cu / bpc) & ~(size_t)255 : 0;
     const hipError_t le = rip::launch_step(x, r->dtype == RIP_BF16, mom, ext, wide_waves, share,

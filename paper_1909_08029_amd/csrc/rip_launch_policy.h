@@ -9,7 +9,8 @@
 namespace rip {
 namespace policy {
 
-constexpr int kMaxK = 8;  // largest group size with a specialized kernel path
+constexpr int kMaxK = 8;   // largest group size with a specialized kernel path
+constexpr int kCus = 256;  // compute units of an MI355X
 
 // Resident waves per CU at which each unit shape sustained the most HBM
 // bandwidth on MI355X, by group size k (entry 0: groups above kMaxK streamed
@@ -75,11 +76,29 @@ inline int launch_waves(const int32_t* k, const int32_t* act, int32_t units, boo
 // Pairs of 80,007, 1252 tiles: 3.5 and 3.8; of 160,007, 2500 tiles: 4.4, 5.1.)
 constexpr int kOneSlotWork = 1024;
 
+// The cap of a launch of `work` workgroups (one wave each) whose units prefer
+// `cap`.  The preferences are those of long launches; a short one is bound by
+// how its waves fall into rounds, and gains from starting more of them at
+// once.  12 waves per CU instead of the preference (8 or 6 replicas, fp32 /
+// bf16, preference -> 12): all workgroups resident, groups of eight of 640,007
+// with momentum 17.8 -> 15.5 us, pairs of 320,007 with it 10.7 -> 8.8; up to
+// 20 per CU, groups of four with momentum 19.6 -> 18.8 (at 39 per CU 36.2 and
+// 36.5); up to 80 per CU, preference 10, lone updates of 2.5M 36.4 -> 35.4,
+// groups of four 38.6 -> 38.3 (at 153 per CU 74.4 and 74.7).
+// Not where 12 per CU leave no slot over (4 fp32 replicas of 1M, a triple and
+// a lone update, 12.0 per CU: 8.64 us at 10, 8.88 at 12), nor for bf16 with
+// momentum at a preference of 10 (lone updates of 640,007: 7.9 and 8.8).
+constexpr int kShortWaves = 12;
+inline int short_cap(int cap, int64_t work, bool bf16_mom) {
+  const int64_t per_cu = (work + kCus - 1) / kCus;
+  const int most = cap >= 10 ? (bf16_mom ? 0 : 80) : (cap >= 8 ? 20 : kShortWaves);
+  return cap < kShortWaves && per_cu <= most && per_cu != kShortWaves ? kShortWaves : cap;
+}
+
 // The wide kernel's launch (units above kMaxK members): waves per workgroup
 // and workgroups per CU.
 constexpr int kWideWaves = 16;  // most waves of a workgroup
 constexpr int kWideC = 4;       // most members a wave holds at once
-constexpr int kCus = 256;       // compute units of an MI355X
 // Most waves of a wide launch that also takes a step's smaller units, most of
 // whose waves have no member (a second launch costs about 2 us; a group of 16
 // beside a lone update of 300,077, 9.4k waves: 11.2 us, 13.7 as two launches;

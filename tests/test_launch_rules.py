@@ -1,0 +1,56 @@
+"""Rules of rip_launch_policy.h for short launches and groups above eight,
+built and run on the CPU."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PROGRAM = r"""
+#include <cstdio>
+#include <initializer_list>
+#include "rip_launch_policy.h"
+using namespace rip::policy;
+int bad = 0;
+#define CHECK(x) do { if (!(x)) { std::printf("failed: %s\n", #x); ++bad; } } while (0)
+int main() {
+  for (int k = kMaxK + 1; k <= 256; ++k)
+    for (int64_t work : {1, 255, 256, 257, 513, 2048, 1 << 20})
+      for (int mom = 0; mom < 2; ++mom) {
+        const WidePlan p = wide_plan(k, work, mom);
+        CHECK(p.waves >= 1 && p.waves <= kWideWaves);
+        CHECK(p.per_cu >= 1 && p.per_cu * p.waves <= 32);
+        CHECK(p.per_cu == 1 || p.per_cu % 2 == 0);
+        for (int j = 1; j <= k; ++j) {  // every unit of the launch
+          const int c = wide_share(j, p.waves);
+          CHECK(c >= 1 && c <= kWideC);
+          const int rounds = (j + kWideC * p.waves - 1) / (kWideC * p.waves);
+          CHECK(c * p.waves * rounds >= j);
+        }
+      }
+  for (int cap = 2; cap <= 14; cap += 2)
+    for (int64_t work : {1, 2560, 2816, 2817, 3072, 5120, 5121, 20480, 20481, 1 << 24}) {
+      const int c = short_cap(cap, work, false);
+      CHECK(c == cap || (c == kShortWaves && cap < kShortWaves));
+      CHECK(c == cap || work <= 80 * kCus);
+      CHECK(work > 2816 || c >= kShortWaves);
+      CHECK(work <= 2816 || work > 3072 || c == cap);
+    }
+  CHECK(short_cap(10, 256, true) == 10 && short_cap(8, 256, true) == kShortWaves);
+  std::printf(bad ? "%d failed\n" : "ok\n", bad);
+  return bad != 0;
+}
+"""
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_short_launches_and_wide_plans(tmp_path):
+    src, exe = tmp_path / "p.cpp", tmp_path / "p"
+    src.write_text(PROGRAM)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-I",
+                    os.path.join(ROOT, "paper_1909_08029_amd", "csrc"), str(src), "-o", str(exe)],
+                   check=True, timeout=120)
+    res = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
+    assert res.returncode == 0, res.stdout
