@@ -219,22 +219,16 @@ struct Header {
 
 __device__ __forceinline__ int lane_id() { return (int)threadIdx.x & (kBlock - 1); }
 
-// The last element of a bf16 tile of odd size: the low half of a dword that
-// the tile's descriptors leave out (so the vector's dword holds 0).  It is in
-// slot e / 64 of lane e % 64, e its vector.
+// The last element of a bf16 tile of odd size is the low half of a dword.  The
+// loads take that dword whole: an aligned dword lies in one page, so what
+// follows the element can be read, and it is never stored.  The stores leave
+// the dword out and store the element alone, from slot e / 64 of lane e % 64,
+// e its vector.  (Loaded alone too, it cost the ragged waves another round of
+// loads and code of their own: 8 lone bf16 replicas of 2,007 2.19 us a launch,
+// now 1.95; one group of 256 of 65,539 31.7, now 25.6.)
+__device__ __forceinline__ int load_bytes(int bytes) { return (bytes + 3) & ~3; }
 constexpr int kOutside = 0x7FFFFFF0;  // a byte offset past every tile
 
-template <int U, typename F>
-__device__ __forceinline__ void odd_load(const char* tile, int bytes, F&& vec) {
-  const int at = bytes - 2, e = at >> 4, word = (at >> 2) & 3;
-  const int off = (e & (kBlock - 1)) == lane_id() ? at : kOutside;
-  const uint32_t x = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(tile_rsrc(tile, bytes), off, 0,
-                                                                    kNonTemporal);
-#pragma unroll
-  for (int u = 0; u < U; ++u)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) vec(u)[i] |= (u == e / kBlock && i == word) ? x : 0u;
-}
 template <int U, typename F>
 __device__ __forceinline__ void odd_store(char* tile, int bytes, F&& vec) {
   const int at = bytes - 2, e = at >> 4, word = (at >> 2) & 3;
@@ -287,10 +281,9 @@ __device__ __forceinline__ void load_members(const Header& h, uint64_t ids, uint
 // (the last tile of a segment: what is left of it).
 //
 // A ragged end needs no code of its own: the descriptors end at the last
-// whole dword, and the hardware checks each dword of an access against that
-// (a dword beyond loads as 0 and is not stored).  Only a bf16 segment of odd
-// size has an element left after that, which the lane of its vector loads and
-// stores by itself.  (Element by element, each member's loads after the last
+// dword, and the hardware checks each dword of an access against that (a dword
+// beyond loads as 0 and is not stored).  Only a bf16 segment of odd size has
+// an element in half a dword, which the lane of its vector stores by itself.  (Element by element, each member's loads after the last
 // one's, a ragged tile held its wave for tens of microseconds: 16 fp32
 // replicas of 304,327 with momentum, weight decay and groups of four 20.5 us
 // a step, now 19.1, and 18.4 with a size that ends on a tile; the same as 59
@@ -316,24 +309,12 @@ __device__ __forceinline__ void tile_slots(Members& m, int64_t tile_byte, int by
   for (int u = 0; u < U; ++u)
 #pragma unroll
     for (int j = 0; j < K; ++j) {
-      wv[u][j] = bld16(tile_rsrc(m.w[j], bytes & ~3), off[u]);
+      wv[u][j] = bld16(tile_rsrc(m.w[j], load_bytes(bytes)), off[u]);
       if (m.active(j)) {
-        gv[u][j] = bld16(tile_rsrc(m.g[j], bytes & ~3), off[u]);
-        if constexpr (MOM) vv[u][j] = bld16(tile_rsrc(m.v[j], bytes & ~3), off[u]);
+        gv[u][j] = bld16(tile_rsrc(m.g[j], load_bytes(bytes)), off[u]);
+        if constexpr (MOM) vv[u][j] = bld16(tile_rsrc(m.v[j], load_bytes(bytes)), off[u]);
       }
     }
-  if constexpr (BF16) {
-    if (__builtin_expect(odd, 0)) {
-#pragma unroll
-      for (int j = 0; j < K; ++j) {
-        odd_load<U>(m.w[j], bytes, [&](int u) -> u32x4& { return wv[u][j]; });
-        if (m.active(j)) {
-          odd_load<U>(m.g[j], bytes, [&](int u) -> u32x4& { return gv[u][j]; });
-          if constexpr (MOM) odd_load<U>(m.v[j], bytes, [&](int u) -> u32x4& { return vv[u][j]; });
-        }
-      }
-    }
-  }
   // From here on the flags and the descriptors' size are new values to the
   // compiler: a descriptor (four scalar registers) lives for its loads only
   // and is put together again for its stores, and a flag is tested where it
@@ -572,7 +553,7 @@ __global__ __launch_bounds__(kBlock) void fused_step_kernel(StepArgs) {
 // number of streams open at once where it is large.  Single waves that took
 // the members in chunks of eight one after the other waited for every chunk's
 // loads by themselves and left most of the chip idle on small replicas: 256
-// bf16 replicas of 65,539 93.2 us, now 32.0; 64 fp32 of 10,000 21.8, now 7.0;
+// bf16 replicas of 65,539 93.2 us, now 25.6; 64 fp32 of 10,000 21.8, now 7.0;
 // 9 fp32 of 4M 85.1, now 70.2; 32 fp32 of 25.6M 1757, now 1702 (5.8 TB/s);
 // groups of 12 to 16 of 8M and more are between 5% faster and 3% slower.  Four
 // members a wave: with eight, the updated values of a bf16 wave take 150-185
@@ -666,22 +647,10 @@ __global__ __launch_bounds__(kBlock * kWideWaves) void wide_step_kernel(StepArgs
       u32x4 wv[kWideC], gv[kWideC], vv[kWideC];
 #pragma unroll
       for (int j = 0; j < kWideC; ++j) {
-        if (j < n) wv[j] = bld16(tile_rsrc(m.w[j], bytes & ~3), off);
+        if (j < n) wv[j] = bld16(tile_rsrc(m.w[j], load_bytes(bytes)), off);
         if (m.active(j)) {
-          gv[j] = bld16(tile_rsrc(m.g[j], bytes & ~3), off);
-          if constexpr (MOM) vv[j] = bld16(tile_rsrc(m.v[j], bytes & ~3), off);
-        }
-      }
-      if constexpr (BF16) {
-        if (__builtin_expect(odd, 0)) {
-#pragma unroll
-          for (int j = 0; j < kWideC; ++j) {
-            if (j < n) odd_load<1>(m.w[j], bytes, [&](int) -> u32x4& { return wv[j]; });
-            if (m.active(j)) {
-              odd_load<1>(m.g[j], bytes, [&](int) -> u32x4& { return gv[j]; });
-              if constexpr (MOM) odd_load<1>(m.v[j], bytes, [&](int) -> u32x4& { return vv[j]; });
-            }
-          }
+          gv[j] = bld16(tile_rsrc(m.g[j], load_bytes(bytes)), off);
+          if constexpr (MOM) vv[j] = bld16(tile_rsrc(m.v[j], load_bytes(bytes)), off);
         }
       }
       asm volatile("" : "+s"(m.act));
