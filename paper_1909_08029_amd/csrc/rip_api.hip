@@ -28,7 +28,7 @@ std::atomic<int> g_blocks_per_cu{0};
 // One workgroup per tile up to 2^25 workgroups (2^31 work-items, within the
 // dispatch's 32-bit grid size); beyond that workgroups loop over tiles.  A
 // workgroup that loops ran the bf16 workload 4% slower than one tile each.
-constexpr int kDefaultMaxBlocks = 1 << 25;
+constexpr int kDefaultMaxBlocks = (int)policy::most_blocks(1);
 }  // namespace
 
 int32_t fail(int32_t code, const char* fmt, ...) {
@@ -580,7 +580,7 @@ extern "C" int32_t rip_preduce(const rip_replicas* r, const int32_t* group_offse
   const bool ext = a.wd != 0.0f || a.nesterov != 0;
   auto launch = [&](rip::StepArgs& x, int wide_waves, int per_cu) -> int32_t {
     if (x.work == 0) return RIP_OK;
-    set_grid(x, (uint32_t)max_blocks);
+    set_grid(x, (uint32_t)std::min<int64_t>(max_blocks, rip::policy::most_blocks(wide_waves)));
     if (wide_waves == 0)
       per_cu = rip::policy::short_cap(per_cu, x.work, mom && r->dtype == RIP_BF16);
     const int bpc = forced_bpc > 0 ? forced_bpc : per_cu;

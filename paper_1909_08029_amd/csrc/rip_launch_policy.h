@@ -130,6 +130,10 @@ inline WidePlan wide_plan(int32_t kmax, int64_t work, bool mom) {
   return p;
 }
 
+// Most workgroups of `waves` waves in one launch: 2^31 work-items, within the
+// dispatch's 32-bit grid size.
+constexpr int64_t most_blocks(int waves) { return ((int64_t)1 << 25) / (waves > 1 ? waves : 1); }
+
 // Members per wave and round of a unit of k members on `waves` waves: the
 // rounds' members split evenly.
 inline int wide_share(int32_t k, int waves) {

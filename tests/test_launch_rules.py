@@ -23,6 +23,7 @@ int main() {
         CHECK(p.waves >= 1 && p.waves <= kWideWaves);
         CHECK(p.per_cu >= 1 && p.per_cu * p.waves <= 32);
         CHECK(p.per_cu == 1 || p.per_cu % 2 == 0);
+        CHECK(most_blocks(p.waves) >= 1 && most_blocks(p.waves) * p.waves * 64 <= 1ll << 31);
         for (int j = 1; j <= k; ++j) {  // every unit of the launch
           const int c = wide_share(j, p.waves);
           CHECK(c >= 1 && c <= kWideC);
