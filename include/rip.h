@@ -299,8 +299,9 @@ int32_t rip_local_step(const rip_replicas* r, const int32_t* active, int32_t n_a
  * .. group_offsets[g+1]-1], strictly ascending).  Groups must be disjoint
  * (RIP_E_OVERLAP otherwise).  sgd == NULL is pure P-Reduce; then n_active
  * must be 0.  One kernel launch covers all groups and updates, or two in a row
- * on `stream`: when the step's units prefer residency caps far apart (a Global
- * Division step of pairs and groups of eight, say) and no cap is forced with
+ * on `stream`: when the units of a step that moves 1 GiB or more prefer
+ * residency caps far apart (a Global Division step of pairs and groups of
+ * eight, say) and no cap is forced with
  * rip_set_blocks_per_cu, or when it has groups above eight, which run on a
  * kernel of their own, beside others in more than a small launch.  The units
  * are disjoint, so the result is the same either way.  If the

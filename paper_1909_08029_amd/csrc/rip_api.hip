@@ -49,6 +49,7 @@ struct rip_replicas {
   int32_t n = 0, n_seg = 0, dtype = 0, device = 0;
   int32_t lds_per_cu = 0;  // bytes of LDS per compute unit on `device`
   int64_t numel0 = 0;      // elements of segment 0 (the whole range when flat)
+  int64_t stream_bytes = 0;  // bytes of one replica's parameters
   bool has_grad = false, has_mom = false;
   int64_t tiles[rip::kTileOptions] = {};  // tiles per unit, by slot option
   void* dmem = nullptr;  // ptab [S][N][3] u64 | seg_numel [S] i64 | seg_tile0 [4][S+1] i64
@@ -324,6 +325,7 @@ int32_t create_replicas(int32_t n_replicas, int32_t n_segments, int32_t dtype,
   h->has_mom = mom != nullptr;
   for (int o = 0; o < rip::kTileOptions; ++o) h->tiles[o] = tile0[(size_t)o * (S + 1) + S];
   h->numel0 = numel[0];
+  h->stream_bytes = total * esize;
   h->device = device;
   e = hipDeviceGetAttribute(&h->lds_per_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor,
                             h->device);
@@ -631,10 +633,12 @@ extern "C" int32_t rip_preduce(const rip_replicas* r, const int32_t* group_offse
     }
     return launch(a1, plan.waves, plan.per_cu);
   }
-  // One launch, or two when the units want residency caps far apart (and
-  // no cap is forced).
+  // One launch, or two when the units of a long step want residency caps far
+  // apart (and no cap is forced).
   int w0 = 0, w1 = 0;
   if (forced_bpc == 0 &&
+      rip::policy::long_enough_to_split(rip::policy::step_bytes(shapes.k, shapes.act, shapes.n, mom,
+                                                                r->stream_bytes)) &&
       rip::policy::split_units(shapes.k, shapes.act, shapes.n, mom, part, &w0, &w1)) {
     subset_step(a, part, 0, a0);
     subset_step(a, part, 1, a1);

@@ -141,6 +141,27 @@ inline int wide_share(int32_t k, int waves) {
   return (k + rounds * waves - 1) / (rounds * waves);
 }
 
+// Bytes a step moves: an updating member reads w and g and writes w (and
+// reads and writes v), an averaging one reads and writes w.  `stream_bytes`:
+// the bytes of one replica's parameters.
+inline double step_bytes(const int32_t* k, const int32_t* act, int32_t units, bool mom,
+                         int64_t stream_bytes) {
+  double n = 0.0;
+  for (int32_t u = 0; u < units; ++u) n += act[u] * (mom ? 5.0 : 3.0) + (k[u] - act[u]) * 2.0;
+  return n * (double)stream_bytes;
+}
+
+// Whether a step is long enough to be split in two by the rule below: the
+// second launch's ramp and tail cost a few microseconds, the better caps gain
+// 1 to 5%.  Steps of a group of eight beside pairs, triples and lone updates,
+// one launch at the mean cap against two: 12,293 elements 2.4 us against 4.3
+// (fp32), 3.3 and 5.5 (momentum); 400,000 10.0 and 11.7; 12 fp32 replicas of
+// 2.4M, 0.35 GB, 57.2 and 59.3; 24 with momentum of 1.2M, 0.58 GB, 103.1 and
+// 104.5; 18 with momentum of 2.4M, 0.86 GB, 150.3 and 149.2; 28 with momentum
+// of 2.4M, 1.3 GB, 231.6 and 225.3, of 5M 501 and 476.
+constexpr double kSplitMinBytes = 1 << 30;
+inline bool long_enough_to_split(double bytes) { return bytes >= kSplitMinBytes; }
+
 // A step whose units prefer caps far apart (Global Division and Inter-Intra
 // steps mix groups of two to eight, and lone updates, in one launch) runs
 // as two launches, each at the cap of its own units: the units preferring

@@ -206,19 +206,26 @@ def test_other_schedulers_small(mode, kw):
 
 @pytest.mark.parametrize("dtype,mom", [(DTYPE_F32, 0.9), (DTYPE_F32, 0.0), (DTYPE_BF16, 0.9)])
 def test_split_launches_global_division(dtype, mom):
-    """Global Division with groups of two to eight: steps whose units want
-    residency caps far apart run as two launches (checked through the launch
-    count the library reports); every element matches the oracle."""
+    """Global Division with groups of two to eight: long steps whose units want
+    residency caps far apart run as two launches, short ones as one (checked
+    through the launch count the library reports); every element of the short
+    steps and sampled windows of the long ones match the oracle."""
     n = 16
-    w = wl.scaled(wl.WORKLOADS[4], [3 * 4096 + 77], steps=16, n=n, dtype=dtype, momentum=mom,
+    short = wl.scaled(wl.WORKLOADS[4], [3 * 4096 + 77], steps=16, n=n, dtype=dtype, momentum=mom,
                   lr=0.1 if dtype == DTYPE_F32 else 20.0,
                   param_sigma=1.0 if dtype == DTYPE_F32 else 0.05,
                   sched=dict(mode=wl.GD, seed=12, kmin=2, kmax=8))
     log(f"case split launches dtype={dtype} momentum={mom}")
-    run = DeviceRun(w)
-    run.run(w.steps)
+    run = DeviceRun(short)
+    run.run(short.steps)
+    assert set(run.launches) == {1}, run.launches
+    check_against_oracle(run, full_windows(short.numel), f"short dtype={dtype} mom={mom}")
+    long = wl.scaled(short, [8_000_077])
+    run = DeviceRun(long)
+    run.run(long.steps)
     assert 2 in run.launches and 1 in run.launches, run.launches
-    check_against_oracle(run, full_windows(w.numel), f"split dtype={dtype} mom={mom}")
+    check_against_oracle(run, sample_windows(long.numel, 12, 8192, 5),
+                         f"split dtype={dtype} mom={mom}")
 
 
 def test_allreduce_and_max_replicas():

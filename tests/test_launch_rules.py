@@ -40,6 +40,17 @@ int main() {
       CHECK(work <= 2816 || work > 3072 || c == cap);
     }
   CHECK(short_cap(10, 256, true) == 10 && short_cap(8, 256, true) == kShortWaves);
+  // a short step stays one launch, whatever its units prefer
+  {
+    const int32_t k[] = {8, 2, 1, 1};
+    for (int mom = 0; mom < 2; ++mom) {
+      CHECK(step_bytes(k, k, 4, mom, 4000) == 12 * (mom ? 20000.0 : 12000.0));
+      CHECK(!long_enough_to_split(step_bytes(k, k, 4, mom, 4 * 1200000)));
+      CHECK(long_enough_to_split(step_bytes(k, k, 4, mom, 4 * 8000000)));
+    }
+    const int32_t none[] = {0, 0, 0, 0};
+    CHECK(step_bytes(k, none, 4, false, 1000) == 24000);
+  }
   std::printf(bad ? "%d failed\n" : "ok\n", bad);
   return bad != 0;
 }
