@@ -7,13 +7,14 @@
 //
 // Work decomposition.  Every unit touches the same element range of its
 // members' buffers, so the launch is a list of (unit, tile) work items, one
-// per single-wave workgroup, unit after unit.  A tile is 64 lanes x 1-8
+// per single-wave workgroup, unit after unit.  A tile is 64 lanes x 1-4
 // slots x 16 bytes of each member stream; the slot count shrinks as the
 // unit's number of streams grows (see slot_log2), so every lane keeps 8-16
 // 16-byte loads in flight (24 for a group of eight with momentum).  The host
-// caps residency per launch at 4-14 waves per CU (an LDS reservation), fewer
-// when the units read more streams: HBM3E delivered its best rate at a bounded
-// depth of outstanding requests, not at full occupancy.  Groups above eight
+// caps residency per launch at 4-12 waves per CU (an LDS reservation; 16 where
+// that many hold the whole launch), fewer when the units read more streams:
+// HBM3E delivered its best rate at a bounded depth of outstanding requests, not
+// at full occupancy.  Groups above eight
 // have a kernel of their own (wide_step_kernel).
 // A workgroup handles one unit, so the unit's size k, its member ids and their active
 // flags are wave-uniform: they sit in scalar registers and every branch on

@@ -78,21 +78,27 @@ constexpr int kOneSlotWork = 1024;
 
 // The cap of a launch of `work` workgroups (one wave each) whose units prefer
 // `cap`.  The preferences are those of long launches; a short one is bound by
-// how its waves fall into rounds, and gains from starting more of them at
-// once.  12 waves per CU instead of the preference (8 or 6 replicas, fp32 /
-// bf16, preference -> 12): all workgroups resident, groups of eight of 640,007
-// with momentum 17.8 -> 15.5 us, pairs of 320,007 with it 10.7 -> 8.8; up to
-// 20 per CU, groups of four with momentum 19.6 -> 18.8 (at 39 per CU 36.2 and
-// 36.5); up to 80 per CU, preference 10, lone updates of 2.5M 36.4 -> 35.4,
-// groups of four 38.6 -> 38.3 (at 153 per CU 74.4 and 74.7).
-// Not where 12 per CU leave no slot over (4 fp32 replicas of 1M, a triple and
-// a lone update, 12.0 per CU: 8.64 us at 10, 8.88 at 12), nor for bf16 with
-// momentum at a preference of 10 (lone updates of 640,007: 7.9 and 8.8).
+// how its waves fall into rounds.  Up to 16 per CU, which the registers of
+// every variant of the kernel allow, all of them start at once.  (1182 random
+// launches of 3 to 16 workgroups per CU, groups of 1 to 8, both types, each
+// timed at caps of 4 to 20; mean over the launches of the time above the best
+// cap of each: at the preference 4.4%, at 12 1.7%, at 16 0.6%, at 20 0.6%.
+// Groups of eight with momentum of 196,608 11.5 us at the preference, 9.4 at
+// 16; pairs of 753,664 bf16 with it, 12 per CU, 11.3 at 10, 10.5 at 14.)
+// Beyond, launches that prefer 8 take 12 up to 24 per CU (83 launches: 1.9%
+// above the best at 8, 1.6 at 12; 16 replicas of 304,327 in 59 tensors, groups
+// of four with momentum, 17.3 us and 16.9), and launches that prefer 10 take
+// 12 up to 80 per CU, or 48 for bf16 with momentum (524 launches of 16 to 80: 2.1% above the best at 10, 1.2 at 12,
+// 2.2 at 16; lone updates of 2.6M 39.0 us and 37.9; bf16 with momentum up to
+// 48: 2.0% and 0.7, from 48 to 80 1.1 and 1.6).  The lower preferences hold as
+// they are (333 launches of 16 to 80: 1.5%, at 12 3.6).
+constexpr int kAllWaves = 16;
 constexpr int kShortWaves = 12;
 inline int short_cap(int cap, int64_t work, bool bf16_mom) {
   const int64_t per_cu = (work + kCus - 1) / kCus;
-  const int most = cap >= 10 ? (bf16_mom ? 0 : 80) : (cap >= 8 ? 20 : kShortWaves);
-  return cap < kShortWaves && per_cu <= most && per_cu != kShortWaves ? kShortWaves : cap;
+  if (per_cu <= kAllWaves) return cap > kAllWaves ? cap : kAllWaves;
+  const int64_t most = cap == 10 ? (bf16_mom ? 48 : 80) : (cap == 8 ? 24 : 0);
+  return per_cu <= most ? kShortWaves : cap;
 }
 
 // The wide kernel's launch (units above kMaxK members): waves per workgroup

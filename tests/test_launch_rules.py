@@ -31,15 +31,22 @@ int main() {
           CHECK(c * p.waves * rounds >= j);
         }
       }
-  for (int cap = 2; cap <= 14; cap += 2)
-    for (int64_t work : {1, 2560, 2816, 2817, 3072, 5120, 5121, 20480, 20481, 1 << 24}) {
-      const int c = short_cap(cap, work, false);
-      CHECK(c == cap || (c == kShortWaves && cap < kShortWaves));
-      CHECK(c == cap || work <= 80 * kCus);
-      CHECK(work > 2816 || c >= kShortWaves);
-      CHECK(work <= 2816 || work > 3072 || c == cap);
+  // short launches: all workgroups at once up to 16 per CU whatever the units
+  // prefer and whatever they store, and never a higher cap for a longer launch
+  for (int cap = 2; cap <= 12; cap += 2)
+    for (int bf16_mom = 0; bf16_mom < 2; ++bf16_mom) {
+      int last = kAllWaves;
+      for (int64_t work = 1; work <= 100 * kCus; work += work < 2600 ? 1 : 17) {
+        const int c = short_cap(cap, work, bf16_mom);
+        CHECK(c >= cap && c <= last);
+        CHECK(work > 16 * kCus || c == kAllWaves);
+        CHECK(work <= 16 * kCus || c == cap || (cap >= 8 && cap <= 10 && c == kShortWaves));
+        CHECK(work <= 80 * kCus || c == cap);
+        last = c;
+      }
     }
-  CHECK(short_cap(10, 256, true) == 10 && short_cap(8, 256, true) == kShortWaves);
+  CHECK(short_cap(10, 40 * kCus, true) == 12 && short_cap(10, 60 * kCus, true) == 10);
+  CHECK(short_cap(10, 60 * kCus, false) == 12);
   // a short step stays one launch, whatever its units prefer
   {
     const int32_t k[] = {8, 2, 1, 1};
