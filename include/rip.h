@@ -339,9 +339,10 @@ int32_t rip_step(rip_sched* s, const rip_replicas* r, int64_t step, const uint8_
  * workgroups, beyond which workgroups loop over tiles); rip_set_blocks_per_cu
  * caps how many of the kernel's workgroups share a compute unit (0 = the
  * default: chosen per launch from its units' sizes, whether their members
- * update, and momentum, 4-12 per compute unit, 16 in a launch of that many or
- * fewer; 1-10 of the several-wave workgroups of groups above eight).  Negative values are
- * RIP_E_INVAL.  Results never depend on these settings. */
+ * update, momentum, and whether the handle has several segments: 4-14 per
+ * compute unit, 16 in a launch of that many or fewer; 1-10 of the several-wave
+ * workgroups of groups above eight).  Negative values are RIP_E_INVAL.
+ * Results never depend on these settings. */
 int32_t rip_set_max_blocks(int32_t max_blocks);
 int32_t rip_set_blocks_per_cu(int32_t blocks_per_cu);
 

@@ -593,6 +593,7 @@ extern "C" int32_t rip_preduce(const rip_replicas* r, const int32_t* group_offse
     ++rip::g_last_launches;
     return RIP_OK;
   };
+  const bool segs = r->n_seg > 1;
   uint8_t part[RIP_MAX_REPLICAS];
   rip::StepArgs a0, a1;
   // Groups above kMaxK run on a kernel of their own.  A step that also has
@@ -619,7 +620,7 @@ extern "C" int32_t rip_preduce(const rip_replicas* r, const int32_t* group_offse
           rest.act[rest.n++] = shapes.act[u];
         }
       subset_step(a, part, 0, a0);
-      const int cap = rip::policy::launch_waves(rest.k, rest.act, rest.n, mom);
+      const int cap = rip::policy::launch_waves(rest.k, rest.act, rest.n, mom, segs);
       if ((rc = launch(a0, 0, cap)) != RIP_OK) return rc;
     }
     subset_step(a, part, 1, a1);
@@ -639,13 +640,13 @@ extern "C" int32_t rip_preduce(const rip_replicas* r, const int32_t* group_offse
   if (forced_bpc == 0 &&
       rip::policy::long_enough_to_split(rip::policy::step_bytes(shapes.k, shapes.act, shapes.n, mom,
                                                                 r->stream_bytes)) &&
-      rip::policy::split_units(shapes.k, shapes.act, shapes.n, mom, part, &w0, &w1)) {
+      rip::policy::split_units(shapes.k, shapes.act, shapes.n, mom, part, &w0, &w1, segs)) {
     subset_step(a, part, 0, a0);
     subset_step(a, part, 1, a1);
     if ((rc = launch(a0, 0, w0)) != RIP_OK) return rc;
     return launch(a1, 0, w1);
   }
-  return launch(a, 0, rip::policy::launch_waves(shapes.k, shapes.act, shapes.n, mom));
+  return launch(a, 0, rip::policy::launch_waves(shapes.k, shapes.act, shapes.n, mom, segs));
 }
 
 extern "C" int32_t rip_step(rip_sched* s, const rip_replicas* r, int64_t step,

@@ -11,7 +11,7 @@
 // slots x 16 bytes of each member stream; the slot count shrinks as the
 // unit's number of streams grows (see slot_log2), so every lane keeps 8-16
 // 16-byte loads in flight (24 for a group of eight with momentum).  The host
-// caps residency per launch at 4-12 waves per CU (an LDS reservation; 16 where
+// caps residency per launch at 4-14 waves per CU (an LDS reservation; 16 where
 // that many hold the whole launch), fewer when the units read more streams:
 // HBM3E delivered its best rate at a bounded depth of outstanding requests, not
 // at full occupancy.  Groups above eight

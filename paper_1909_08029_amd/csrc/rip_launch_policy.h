@@ -38,17 +38,31 @@ constexpr int kCus = 256;  // compute units of an MI355X
 constexpr int kWavesSgd[kMaxK + 1] = {4, 10, 10, 8, 10, 8, 8, 6, 6};
 constexpr int kWavesMom[kMaxK + 1] = {4, 10, 10, 10, 8, 6, 4, 4, 4};
 constexpr int kWavesAvg[kMaxK + 1] = {6, 12, 12, 8, 12, 10, 8, 6, 6};
+// Handles of several segments (separate layer tensors) need more waves for some
+// shapes: a wave first finds its segment, a chain of scalar loads that flat
+// replicas don't have, and lanes of a tensor's last tile have nothing to load.
+// On the layer tensors of networks of 1M to 90M elements (44 to 70 handles of
+// 6 to 161 tensors each; time above the best cap, flat entry -> this one): lone
+// updates 2.9% -> 0.2, averaging only, pairs 2.7 -> 0.5, triples 1.6 -> 0.5,
+// groups of seven 7.9 -> 0.0 (flat: 0.2 -> 1.1, 0.0 -> 2.7, 0.1 -> 1.4 and 0.1
+// -> 2.2).
+constexpr int seg_waves_sgd(int k) { return k == 1 ? 12 : kWavesSgd[k]; }
+constexpr int seg_waves_avg(int k) {
+  return k == 2 ? 14 : k == 3 ? 10 : k == 7 ? 8 : kWavesAvg[k];
+}
 
 // The cap used when a launch has no units (nothing is launched then).
 constexpr int kWavesDefault = 8;
 
 // Preferred cap of one unit of k members of which `act` update this step:
 // the averaging-only and all-updating preferences, interpolated by the share
-// of updating members.
-inline double unit_waves(int32_t k, int32_t act, bool mom) {
+// of updating members.  `segs`: the handle has several segments.
+inline double unit_waves(int32_t k, int32_t act, bool mom, bool segs = false) {
   const int idx = k <= kMaxK ? k : 0;
   const double f = (double)act / (double)k;
-  return f * (mom ? kWavesMom[idx] : kWavesSgd[idx]) + (1.0 - f) * kWavesAvg[idx];
+  const int sgd = segs ? seg_waves_sgd(idx) : kWavesSgd[idx];
+  const int avg = segs ? seg_waves_avg(idx) : kWavesAvg[idx];
+  return f * (mom ? kWavesMom[idx] : sgd) + (1.0 - f) * avg;
 }
 
 // Cap of a launch running `units` units (unit u: k[u] members, act[u] of them
@@ -57,11 +71,12 @@ inline double unit_waves(int32_t k, int32_t act, bool mom) {
 // and v; an averaging one w), and the mean is rounded up to an even cap: a cap
 // below a shape's preference cost more (SGD groups of 2-4 at 8 waves: -3%)
 // than one above it (groups of 5-8 at 10: -1%).
-inline int launch_waves(const int32_t* k, const int32_t* act, int32_t units, bool mom) {
+inline int launch_waves(const int32_t* k, const int32_t* act, int32_t units, bool mom,
+                        bool segs = false) {
   double num = 0.0, den = 0.0;
   for (int32_t u = 0; u < units; ++u) {
     const double bytes = act[u] * (mom ? 5.0 : 3.0) + (k[u] - act[u]) * 2.0;
-    num += unit_waves(k[u], act[u], mom) * bytes;
+    num += unit_waves(k[u], act[u], mom, segs) * bytes;
     den += bytes;
   }
   if (den == 0.0) return kWavesDefault;
@@ -186,14 +201,14 @@ constexpr int kMaxUnits = 256;  // a launch's units are disjoint, so at most the
 // (0: the first launch, preferring >= kSplitCap waves; 1: the second) and
 // the two launches' caps, or returns false (one launch at launch_waves).
 inline bool split_units(const int32_t* k, const int32_t* act, int32_t units, bool mom,
-                        uint8_t* part, int* waves0, int* waves1) {
+                        uint8_t* part, int* waves0, int* waves1, bool segs = false) {
   if (units < kSplitMinUnits || units > kMaxUnits) return false;
   int32_t k0[kMaxUnits], a0[kMaxUnits], k1[kMaxUnits], a1[kMaxUnits];
   int32_t n0 = 0, n1 = 0;
   double b0 = 0.0, b1 = 0.0;
   for (int32_t u = 0; u < units; ++u) {
     const double bytes = act[u] * (mom ? 5.0 : 3.0) + (k[u] - act[u]) * 2.0;
-    if (unit_waves(k[u], act[u], mom) >= kSplitCap - 1e-9) {
+    if (unit_waves(k[u], act[u], mom, segs) >= kSplitCap - 1e-9) {
       part[u] = 0;
       k0[n0] = k[u];
       a0[n0++] = act[u];
@@ -207,8 +222,8 @@ inline bool split_units(const int32_t* k, const int32_t* act, int32_t units, boo
   }
   if (n0 == 0 || n1 == 0) return false;
   if (b0 < kSplitMinShare * (b0 + b1) || b1 < kSplitMinShare * (b0 + b1)) return false;
-  *waves0 = launch_waves(k0, a0, n0, mom);
-  *waves1 = launch_waves(k1, a1, n1, mom);
+  *waves0 = launch_waves(k0, a0, n0, mom, segs);
+  *waves1 = launch_waves(k1, a1, n1, mom, segs);
   return *waves0 - *waves1 >= kSplitMinGap;
 }
 

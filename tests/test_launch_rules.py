@@ -47,6 +47,20 @@ int main() {
     }
   CHECK(short_cap(10, 40 * kCus, true) == 12 && short_cap(10, 60 * kCus, true) == 10);
   CHECK(short_cap(10, 60 * kCus, false) == 12);
+  // separate tensors: more waves where flat replicas lost them, never fewer
+  for (int mom = 0; mom < 2; ++mom)
+    for (int k = 1; k <= kMaxK; ++k)
+      for (int act = 0; act <= k; ++act) {
+        const int32_t ks[] = {k, k}, as[] = {act, k};
+        CHECK(launch_waves(ks, as, 2, mom, true) >= launch_waves(ks, as, 2, mom));
+      }
+  {
+    const int32_t one[] = {1}, two[] = {2}, three[] = {3}, seven[] = {7}, none[] = {0};
+    CHECK(launch_waves(one, one, 1, false, true) == 12);
+    CHECK(launch_waves(two, none, 1, false, true) == 14);
+    CHECK(launch_waves(three, none, 1, false, true) == 10);
+    CHECK(launch_waves(seven, none, 1, false, true) == 8);
+  }
   // a short step stays one launch, whatever its units prefer
   {
     const int32_t k[] = {8, 2, 1, 1};
