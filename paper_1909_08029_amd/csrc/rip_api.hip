@@ -580,11 +580,14 @@ extern "C" int32_t rip_preduce(const rip_replicas* r, const int32_t* group_offse
       rip::g_max_blocks.load() > 0 ? rip::g_max_blocks.load() : rip::kDefaultMaxBlocks;
   const int forced_bpc = rip::g_blocks_per_cu.load();
   const bool ext = a.wd != 0.0f || a.nesterov != 0;
+  int32_t n_lone = 0;
+  for (int32_t u = 0; u < shapes.n; ++u) n_lone += shapes.k[u] == 1;
   auto launch = [&](rip::StepArgs& x, int wide_waves, int per_cu) -> int32_t {
     if (x.work == 0) return RIP_OK;
     set_grid(x, (uint32_t)std::min<int64_t>(max_blocks, rip::policy::most_blocks(wide_waves)));
     if (wide_waves == 0)
-      per_cu = rip::policy::short_cap(per_cu, x.work, mom && r->dtype == RIP_BF16);
+      per_cu = rip::policy::short_cap(per_cu, x.work, mom && r->dtype == RIP_BF16,
+                                      !mom && shapes.n == n_lone);
     const int bpc = forced_bpc > 0 ? forced_bpc : per_cu;
     const size_t share = r->lds_per_cu > 0 ? (size_t)(r->lds_per_cu / bpc) & ~(size_t)255 : 0;
     const hipError_t le = rip::launch_step(x, r->dtype == RIP_BF16, mom, ext, wide_waves, share,

@@ -105,14 +105,17 @@ constexpr int kOneSlotWork = 1024;
 // of four with momentum, 17.3 us and 16.9), and launches that prefer 10 take
 // 12 up to 80 per CU, or 48 for bf16 with momentum (524 launches of 16 to 80: 2.1% above the best at 10, 1.2 at 12,
 // 2.2 at 16; lone updates of 2.6M 39.0 us and 37.9; bf16 with momentum up to
-// 48: 2.0% and 0.7, from 48 to 80 1.1 and 1.6).  The lower preferences hold as
-// they are (333 launches of 16 to 80: 1.5%, at 12 3.6).
+// 48: 2.0% and 0.7, from 48 to 80 1.1 and 1.6).  Plain lone updates, four slots
+// per wave and so the fewest waves, take 12 up to 220 per CU (61 launches of 90
+// to 220: 1.0% above the best at 10, 0.1 at 12; 35 of 220 to 400: 0.3 and 0.5).
+// The lower preferences hold as they are (333 launches of 16 to 80: 1.5%, at 12
+// 3.6).
 constexpr int kAllWaves = 16;
 constexpr int kShortWaves = 12;
-inline int short_cap(int cap, int64_t work, bool bf16_mom) {
+inline int short_cap(int cap, int64_t work, bool bf16_mom, bool lone_sgd = false) {
   const int64_t per_cu = (work + kCus - 1) / kCus;
   if (per_cu <= kAllWaves) return cap > kAllWaves ? cap : kAllWaves;
-  const int64_t most = cap == 10 ? (bf16_mom ? 48 : 80) : (cap == 8 ? 24 : 0);
+  const int64_t most = cap == 10 ? (bf16_mom ? 48 : lone_sgd ? 220 : 80) : (cap == 8 ? 24 : 0);
   return per_cu <= most ? kShortWaves : cap;
 }
 

@@ -47,6 +47,8 @@ int main() {
     }
   CHECK(short_cap(10, 40 * kCus, true) == 12 && short_cap(10, 60 * kCus, true) == 10);
   CHECK(short_cap(10, 60 * kCus, false) == 12);
+  CHECK(short_cap(10, 100 * kCus, false, true) == 12 && short_cap(10, 230 * kCus, false, true) == 10);
+  CHECK(short_cap(10, 100 * kCus, false, false) == 10);
   // separate tensors: more waves where flat replicas lost them, never fewer
   for (int mom = 0; mom < 2; ++mom)
     for (int k = 1; k <= kMaxK; ++k)
