@@ -291,7 +291,7 @@ __device__ __forceinline__ void load_members(const Header& h, uint64_t ids, uint
 // separate tensors 21.7, now 20.0.)
 template <int K, int U, bool BF16, bool MOM, bool EXT>
 __device__ __forceinline__ void tile_slots(Members& m, int64_t tile_byte, int bytes,
-                                           const Opt& o) {
+                                           const Opt& o, int small) {
   using V = Vec<BF16>;
   constexpr int N = V::N;
   constexpr float inv_k = (float)(1.0 / K);
@@ -358,14 +358,20 @@ __device__ __forceinline__ void tile_slots(Members& m, int64_t tile_byte, int by
   __builtin_amdgcn_sched_barrier(0);
   asm volatile("" : "+s"(m.act));
   // A wave of a large group with momentum has 12-16 stores, and issued back
-  // to back they cost the HBM3E rate: 16 cycles between them gave 16 fp32
-  // replicas of 138.4M (groups of eight) 7462 -> 7395 us, groups of six of
-  // 25.6M 1519 -> 1511; with fewer streams the pause itself costs (groups of
-  // eight without momentum -2%, lone updates with it -2%).
-  const auto pace = [] {
+  // to back they cost the HBM3E rate: 16 cycles between them gave groups of
+  // six to eight of 25.6M to 276M elements 0.3-1.5% (eight of 138.4M fp32
+  // 7546 -> 7475 us); with fewer streams the pause itself costs (groups of
+  // eight without momentum -2%, lone updates with it -2%).  So it does in a
+  // launch small enough for one-slot tiles, which leaves HBM idle: up to 512
+  // tiles 5-10% (two groups of eight of 16,384 3.40 us with it, 3.27 skipping
+  // it, 3.20 without any of this; bf16 3.89, 3.70 and 3.57), at 1024 nothing,
+  // beyond that it is ahead.  The branch is inside the asm: one of the
+  // compiler's ends the block, and it sank arithmetic below the stores.
+  const auto pace = [small] {
+    (void)small;
     if constexpr (MOM && K >= 6) {
       __builtin_amdgcn_sched_barrier(0);
-      asm volatile("s_nop 15");
+      asm volatile("s_cmp_lg_u32 %0, 0\n\ts_cbranch_scc1 1f\n\ts_nop 15\n1:" ::"s"(small) : "scc");
       __builtin_amdgcn_sched_barrier(0);
     }
   };
@@ -482,7 +488,8 @@ __device__ __forceinline__ void tile_of(const Header& h, const Unit& u, int64_t 
   constexpr int esize = BF16 ? 2 : 4;
   Members m;
   load_members<K, MOM>(h, u.ids, u.act8, at.seg, m);
-  tile_slots<K, SL, BF16, MOM, EXT>(m, at.e_tile * esize, at.elems * esize, h.opt);
+  tile_slots<K, SL, BF16, MOM, EXT>(m, at.e_tile * esize, at.elems * esize, h.opt,
+                                     h.one_slot);
 }
 template <int K, bool BF16, bool MOM, bool EXT>
 __device__ __forceinline__ void unit_tile(const Header& h, const Unit& u, int64_t tile) {

@@ -8,7 +8,9 @@ rip_kernels.hip to AMDGPU assembly with the library's own flags).
   mode is 3: inputs and outputs preserved), as the exact group mean needs;
 * no fused multiply-add or multiply-accumulate is emitted: every product and
   sum rounds on its own, in the order the oracle follows;
-* no packed fp32 arithmetic is emitted (the library is built without it).
+* no packed fp32 arithmetic is emitted (the library is built without it);
+* the pause between the stores of large momentum groups is skipped by a branch
+  (small launches do not take it).
 """
 import os
 import re
@@ -63,3 +65,10 @@ def test_no_fused_multiply_add(asm):
 def test_no_packed_fp32_arithmetic(asm):
     ins = set(instructions(asm))
     assert not {i for i in ins if i.startswith("v_pk_") and i.endswith("_f32")}
+
+
+def test_the_pause_between_stores_is_conditional(asm):
+    lines = [l.strip() for l in asm.splitlines()]
+    at = [i for i, l in enumerate(lines) if l == "s_nop 15"]
+    assert at
+    assert all(lines[i - 1].startswith("s_cbranch") for i in at)
