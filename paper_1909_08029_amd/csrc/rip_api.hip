@@ -602,16 +602,19 @@ extern "C" int32_t rip_preduce(const rip_replicas* r, const int32_t* group_offse
   // Groups above kMaxK run on a kernel of their own.  A step that also has
   // other units is two launches, each at its own units' cap, or, while one
   // launch of all units on that kernel is small, one.
-  int32_t n_wide = 0, kmax = 0;
+  int32_t n_wide = 0, wide_act = 0, kmax = 0;
   for (int32_t u = 0; u < shapes.n; ++u) {
     part[u] = shapes.k[u] > rip::kMaxK;
     n_wide += part[u];
+    wide_act += part[u] ? shapes.act[u] : 0;
     kmax = std::max(kmax, shapes.k[u]);
   }
   if (n_wide > 0) {
     const int64_t all_work = shapes.n * r->tiles[0];
-    if (n_wide < shapes.n &&
-        all_work * rip::policy::wide_plan(kmax, all_work, mom).waves <= rip::policy::kWideAllWaves) {
+    const bool bf16 = r->dtype == RIP_BF16;
+    if (n_wide < shapes.n && all_work <= rip::policy::kLongWide &&
+        all_work * rip::policy::wide_plan(kmax, all_work, bf16, mom, true).waves <=
+            rip::policy::kWideAllWaves) {
       std::memset(part, 1, sizeof part);
       n_wide = shapes.n;
     }
@@ -629,7 +632,7 @@ extern "C" int32_t rip_preduce(const rip_replicas* r, const int32_t* group_offse
     subset_step(a, part, 1, a1);
     a1.work = 0;
     for (int32_t u = 0; u < a1.n_units; ++u) a1.unit_work0[u + 1] = a1.work += (uint32_t)r->tiles[0];
-    const rip::policy::WidePlan plan = rip::policy::wide_plan(kmax, a1.work, mom);
+    const rip::policy::WidePlan plan = rip::policy::wide_plan(kmax, a1.work, bf16, mom, wide_act > 0);
     for (int32_t u = 0; u < a1.n_units; ++u) {
       const int k = (int)rip::unit_info_k(a1.unit_info[u]);
       a1.unit_info[u] = rip::unit_info_pack(rip::unit_info_base(a1.unit_info[u]), (uint32_t)k,

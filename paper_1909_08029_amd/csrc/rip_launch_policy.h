@@ -133,23 +133,56 @@ struct WidePlan {
   int waves, per_cu;
 };
 
-// Four members per wave as far as the waves go: eight waves, or sixteen when
-// every workgroup has a CU to itself, where only the latency of a workgroup
-// counts (256 bf16 replicas of 65,539: 28.8 us with sixteen, 38.4 with eight),
-// or with momentum (64 fp32 replicas of 4M: 953 us, 985 with eight; with plain
-// SGD, 64 of 600,077: 94.7, with eight 90.6).  Sixteen waves share a CU (fp32
-// groups of 16, 10M: 325 us at 16, 342 at 12, 338 at 20-24), more when that
-// lets all workgroups start at once (24 fp32 replicas of 150,077: 7.3 us with
-// four workgroups of six waves a CU, 9.7 with two).  Workgroups per CU are
-// even (an odd count gets the residency of the even one below).
-inline WidePlan wide_plan(int32_t kmax, int64_t work, bool mom) {
+// Waves of the wide kernel that a CU's registers hold (61, 77, 86 and 104 VGPRs).
+constexpr int wide_resident(bool bf16, bool mom) { return bf16 ? (mom ? 16 : 20) : (mom ? 24 : 32); }
+
+// Short launches, up to 16 workgroups per CU (SGD: 64): four members per wave
+// as far as the waves go: eight waves, or sixteen when every workgroup has a CU
+// to itself, where only the latency of a workgroup counts (256 bf16 replicas of
+// 65,539: 28.8 us with sixteen, 38.4 with eight), or for more than 64 members
+// with momentum.  (For 33 to 64 with it, nine to sixteen waves left one
+// workgroup on a CU: 57 random launches of 1 to 16 workgroups per CU 17% above
+// the best plan of each, 5% with eight.)  Sixteen waves share a CU (fp32 groups
+// of 16, 10M: 325 us at 16, 342 at 12, 338 at 20-24); workgroups of three waves
+// go four to a CU, as in long launches.  A cap that all workgroups fit under,
+// to 32 waves, is lifted to that (24 fp32 replicas of 150,077, four workgroups
+// of six waves per CU, 7.3 us, 9.7 at two); groups of 17 to 64 whose waves the
+// registers do not hold that many of take fewer, down to three, so that they do
+// (78 random launches: 6% less time; more members gained nothing, 9 to 16
+// fit).
+//
+// Longer launches are bound by the streams open at once, and more waves lose
+// what they gain in latency.  1752 random launches (9 to 256 members, 0.5 to
+// 2900 workgroups per CU, both types), each timed with 10 to 30 plans; of those
+// above 64 per CU, time above the best plan of each, four members a wave on
+// eight or sixteen waves -> this plan: SGD, 13 to 24 members 3.3% -> 1.9, 25 to
+// 32 2.1 -> 0.8; averaging, 21 to 24 11 -> 0.9; momentum, 9 to 12 2.0 -> 0.8, 13
+// to 24 4.0 -> 1.2, 25 to 64 3.2 -> 1.2 (single waves that took the members in
+// chunks of eight, all workgroups capped at four per CU, 3 to 5%).  Between 16
+// and 64 per CU momentum gains (33 to 64 members 3.9%, 13 to 24 1.8%), SGD does
+// not (13 to 24 +0.0%, up to 8% slower).  Replicas at a pitch of a power of two
+// (64 MiB and more) stay up to 20% behind those single waves.
+//
+// Workgroups per CU are even (an odd count gets the residency of the even one
+// below).
+constexpr int64_t kLongWide = 16 * kCus;  // workgroups
+inline WidePlan wide_plan(int32_t kmax, int64_t work, bool bf16, bool mom, bool updates) {
   WidePlan p;
-  const int most = mom || work <= kCus ? kWideWaves : kWideWaves / 2;
+  if (work > (mom || !updates ? kLongWide : 4 * kLongWide)) {
+    if (mom) return kmax <= 12 ? WidePlan{2, 6} : kmax <= 24 ? WidePlan{2, 4}
+                  : kmax <= 64 ? WidePlan{3, 2} : WidePlan{kWideWaves, 1};
+    if (kmax <= 12 || (updates && kmax <= 24)) return WidePlan{3, 4};
+    if (kmax <= 32) return updates ? WidePlan{6, 2} : WidePlan{4, 4};
+    return WidePlan{kWideWaves / 2, 2};
+  }
+  const int most = work <= kCus || (mom && kmax > 64) ? kWideWaves : kWideWaves / 2;
   p.waves = (kmax + kWideC - 1) / kWideC;
   if (p.waves > most) p.waves = most;
   const auto even = [](int64_t n) { return n < 2 ? n : (n + 1) / 2 * 2; };
   p.per_cu = (int)(p.waves == 3 ? 4 : even(16 / p.waves));
   const int64_t all = even((work + kCus - 1) / kCus);
+  const int64_t fit = wide_resident(bf16, mom) / all;
+  if (kmax > 16 && kmax <= 64 && p.waves > fit && fit >= 3) p.waves = (int)fit;
   if (all > p.per_cu && all * p.waves <= 32) p.per_cu = (int)all;
   return p;
 }

@@ -10,7 +10,9 @@ rip_kernels.hip to AMDGPU assembly with the library's own flags).
   sum rounds on its own, in the order the oracle follows;
 * no packed fp32 arithmetic is emitted (the library is built without it);
 * the pause between the stores of large momentum groups is skipped by a branch
-  (small launches do not take it).
+  (small launches do not take it);
+* the registers of the kernel of groups above eight hold the waves per CU that
+  the launch policy counts on.
 """
 import os
 import re
@@ -72,3 +74,17 @@ def test_the_pause_between_stores_is_conditional(asm):
     at = [i for i, l in enumerate(lines) if l == "s_nop 15"]
     assert at
     assert all(lines[i - 1].startswith("s_cbranch") for i in at)
+
+
+def test_waves_of_the_wide_kernel_that_registers_hold(asm):
+    with open(os.path.join(ROOT, "paper_1909_08029_amd", "csrc", "rip_launch_policy.h")) as f:
+        m = re.search(r"int wide_resident\(bool bf16, bool mom\) \{ return bf16 \? "
+                      r"\(mom \? (\d+) : (\d+)\) : \(mom \? (\d+) : (\d+)\); \}", f.read())
+    bf16_mom, bf16_sgd, f32_mom, f32_sgd = (int(x) for x in m.groups())
+    want = {("1", "1"): bf16_mom, ("1", "0"): bf16_sgd, ("0", "1"): f32_mom, ("0", "0"): f32_sgd}
+    vgprs = re.findall(r"wide_step_kernelILb(\d)ELb(\d)ELb\dE\S+\n(?:.*\n)*?\s+\.vgpr_count:\s+(\d+)",
+                       asm[asm.index("amdhsa.kernels:"):])
+    assert len(vgprs) == 8
+    for bf16, mom, v in vgprs:
+        # 512 registers per lane and SIMD, in blocks of eight; four SIMDs
+        assert 4 * min(8, 512 // (-(-int(v) // 8) * 8)) == want[bf16, mom], (bf16, mom, v)

@@ -17,18 +17,30 @@ int bad = 0;
 #define CHECK(x) do { if (!(x)) { std::printf("failed: %s\n", #x); ++bad; } } while (0)
 int main() {
   for (int k = kMaxK + 1; k <= 256; ++k)
-    for (int64_t work : {1, 255, 256, 257, 513, 2048, 1 << 20})
+    for (int64_t work : {1, 255, 256, 257, 513, 2048, 4096, 4097, 16384, 16385, 1 << 20})
       for (int mom = 0; mom < 2; ++mom) {
-        const WidePlan p = wide_plan(k, work, mom);
-        CHECK(p.waves >= 1 && p.waves <= kWideWaves);
-        CHECK(p.per_cu >= 1 && p.per_cu * p.waves <= 32);
-        CHECK(p.per_cu == 1 || p.per_cu % 2 == 0);
-        CHECK(most_blocks(p.waves) >= 1 && most_blocks(p.waves) * p.waves * 64 <= 1ll << 31);
-        for (int j = 1; j <= k; ++j) {  // every unit of the launch
-          const int c = wide_share(j, p.waves);
-          CHECK(c >= 1 && c <= kWideC);
-          const int rounds = (j + kWideC * p.waves - 1) / (kWideC * p.waves);
-          CHECK(c * p.waves * rounds >= j);
+        for (int form = 0; form < 4; ++form) {
+          const bool bf16 = form & 1, updates = form & 2;
+          const WidePlan p = wide_plan(k, work, bf16, mom, updates);
+          CHECK(p.waves >= 1 && p.waves <= kWideWaves);
+          CHECK(p.per_cu >= 1 && p.per_cu * p.waves <= 32);
+          CHECK(p.per_cu == 1 || p.per_cu % 2 == 0);
+          CHECK(most_blocks(p.waves) >= 1 && most_blocks(p.waves) * p.waves * 64 <= 1ll << 31);
+          for (int j = 1; j <= k; ++j) {  // every unit of the launch
+            const int c = wide_share(j, p.waves);
+            CHECK(c >= 1 && c <= kWideC);
+            const int rounds = (j + kWideC * p.waves - 1) / (kWideC * p.waves);
+            CHECK(c * p.waves * rounds >= j);
+          }
+          // where workgroups share a CU the registers hold two of them (16 waves
+          // in the largest variant), and all of them where three waves will do;
+          // long launches count on no more
+          const int64_t all = (work + 2 * kCus - 1) / (2 * kCus) * 2;
+          CHECK(work <= kCus || p.waves <= 8 || (mom && k > 64));
+          if (work > kCus && k > 16 && k <= 64 && all * 3 <= wide_resident(bf16, mom))
+            CHECK(all * p.waves <= wide_resident(bf16, mom));
+          CHECK(work <= 4 * kLongWide || p.waves * p.per_cu <= 16);
+          CHECK(work <= kLongWide || !mom || p.waves * p.per_cu <= 16);
         }
       }
   // short launches: all workgroups at once up to 16 per CU whatever the units
