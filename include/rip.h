@@ -28,10 +28,10 @@
  *    work is asynchronous on that stream.
  *  - Handles are not thread-safe; use one handle per thread or lock.
  *  - Graph capture: rip_local_step and rip_preduce enqueue one kernel
- *    launch (two for a step that mixes unit shapes with far-apart residency
- *    preferences, or groups above eight with other units; nothing when the
- *    step has no work), each with its part of the step -- schedule, optimizer scalars, the handle's pointer table --
- *    in the kernel argument, and no memset, copy or allocation.  They may be
+ *    launch (up to three for a step of several unit shapes, see rip_preduce;
+ *    nothing when the step has no work), each with its part of the step --
+ *    schedule, optimizer scalars, the handle's pointer table -- in the kernel
+ *    argument, and no memset, copy or allocation.  They may be
  *    called on a stream under HIP graph capture; each replay re-applies the
  *    captured step to whatever the buffers hold then.  The replicas handle
  *    must outlive the graph.
@@ -73,7 +73,7 @@ const char* rip_last_error(void);
 int32_t rip_abi_version(void);
 /* Kernel launches the calling thread's last rip_preduce, rip_local_step or
  * rip_step enqueued: 0 (an error before any launch, or a step with no work),
- * 1, or 2 (a step split by its units' sizes; see rip_preduce).  For
+ * 1, or 2 or 3 (a step split by its units' sizes; see rip_preduce).  For
  * accounting and tests; results never depend on it. */
 int32_t rip_last_launch_count(void);
 
@@ -298,14 +298,15 @@ int32_t rip_local_step(const rip_replicas* r, const int32_t* active, int32_t n_a
  * of the `n_groups` groups given as CSR (group g = members[group_offsets[g]
  * .. group_offsets[g+1]-1], strictly ascending).  Groups must be disjoint
  * (RIP_E_OVERLAP otherwise).  sgd == NULL is pure P-Reduce; then n_active
- * must be 0.  One kernel launch covers all groups and updates, or two in a row
- * on `stream`: when the units of a step that moves 1 GiB or more prefer
+ * must be 0.  One kernel launch covers all groups and updates, with two
+ * exceptions, each of which adds one, in a row on `stream`: groups above eight
+ * run on a kernel of their own, beside other units in more than a small launch;
+ * and where the units of up to eight members move 1 GiB or more and prefer
  * residency caps far apart (a Global Division step of pairs and groups of
- * eight, say) and no cap is forced with
- * rip_set_blocks_per_cu, or when it has groups above eight, which run on a
- * kernel of their own, beside others in more than a small launch.  The units
- * are disjoint, so the result is the same either way.  If the
- * second of two launches fails, the first has been enqueued (RIP_E_HIP).
+ * eight, say), they are two launches, unless a cap is forced with
+ * rip_set_blocks_per_cu.  The units are disjoint, so the result is the same
+ * either way.  If a launch fails, those before it have been enqueued
+ * (RIP_E_HIP).
  * Errors: RIP_E_INVAL (also: the current device is not the handle's),
  * RIP_E_OVERLAP, RIP_E_UNSUPPORTED (a step of 2^31 or more tiles), RIP_E_HIP
  * (launch failure). */

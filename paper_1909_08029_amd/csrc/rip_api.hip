@@ -596,63 +596,64 @@ extern "C" int32_t rip_preduce(const rip_replicas* r, const int32_t* group_offse
     ++rip::g_last_launches;
     return RIP_OK;
   };
-  const bool segs = r->n_seg > 1;
-  uint8_t part[RIP_MAX_REPLICAS];
-  rip::StepArgs a0, a1;
-  // Groups above kMaxK run on a kernel of their own.  A step that also has
-  // other units is two launches, each at its own units' cap, or, while one
-  // launch of all units on that kernel is small, one.
+  const bool segs = r->n_seg > 1, bf16 = r->dtype == RIP_BF16;
+  // Groups above kMaxK run on a kernel of their own, unless one launch of all
+  // units on that kernel is small.
+  uint8_t part[RIP_MAX_REPLICAS];  // 0, 1: launches of up to kMaxK members; 2: groups above
   int32_t n_wide = 0, wide_act = 0, kmax = 0;
   for (int32_t u = 0; u < shapes.n; ++u) {
-    part[u] = shapes.k[u] > rip::kMaxK;
-    n_wide += part[u];
-    wide_act += part[u] ? shapes.act[u] : 0;
+    const bool wide = shapes.k[u] > rip::kMaxK;
+    part[u] = wide ? 2 : 0;
+    n_wide += wide;
+    wide_act += wide ? shapes.act[u] : 0;
     kmax = std::max(kmax, shapes.k[u]);
   }
-  if (n_wide > 0) {
-    const int64_t all_work = shapes.n * r->tiles[0];
-    const bool bf16 = r->dtype == RIP_BF16;
-    if (n_wide < shapes.n && all_work <= rip::policy::kLongWide &&
-        all_work * rip::policy::wide_plan(kmax, all_work, bf16, mom, true).waves <=
-            rip::policy::kWideAllWaves) {
-      std::memset(part, 1, sizeof part);
-      n_wide = shapes.n;
+  const int64_t all_work = shapes.n * r->tiles[0];
+  if (n_wide > 0 && all_work <= rip::policy::kLongWide &&
+      all_work * rip::policy::wide_plan(kmax, all_work, bf16, mom, true).waves <=
+          rip::policy::kWideAllWaves) {
+    std::memset(part, 2, sizeof part);
+    n_wide = shapes.n;
+  }
+  // The other units: one launch, or two when those of a long step want
+  // residency caps far apart (and no cap is forced).
+  rip::StepArgs a0, a1;
+  if (n_wide < shapes.n) {
+    UnitShapes rest;
+    uint8_t unit[RIP_MAX_REPLICAS], half[RIP_MAX_REPLICAS];
+    for (int32_t u = 0; u < shapes.n; ++u) {
+      if (part[u] != 0) continue;
+      unit[rest.n] = (uint8_t)u;
+      rest.k[rest.n] = shapes.k[u];
+      rest.act[rest.n++] = shapes.act[u];
     }
-    if (n_wide < shapes.n) {
-      UnitShapes rest;
-      for (int32_t u = 0; u < shapes.n; ++u)
-        if (!part[u]) {
-          rest.k[rest.n] = shapes.k[u];
-          rest.act[rest.n++] = shapes.act[u];
-        }
+    int w0 = 0, w1 = 0;
+    if (forced_bpc == 0 &&
+        rip::policy::long_enough_to_split(
+            rip::policy::step_bytes(rest.k, rest.act, rest.n, mom, r->stream_bytes)) &&
+        rip::policy::split_units(rest.k, rest.act, rest.n, mom, half, &w0, &w1, segs)) {
+      for (int32_t i = 0; i < rest.n; ++i) part[unit[i]] = half[i];
       subset_step(a, part, 0, a0);
-      const int cap = rip::policy::launch_waves(rest.k, rest.act, rest.n, mom, segs);
-      if ((rc = launch(a0, 0, cap)) != RIP_OK) return rc;
+      subset_step(a, part, 1, a1);
+      if ((rc = launch(a0, 0, w0)) != RIP_OK || (rc = launch(a1, 0, w1)) != RIP_OK) return rc;
+    } else {
+      if (n_wide > 0) subset_step(a, part, 0, a0);
+      rc = launch(n_wide > 0 ? a0 : a, 0,
+                  rip::policy::launch_waves(rest.k, rest.act, rest.n, mom, segs));
+      if (rc != RIP_OK) return rc;
     }
-    subset_step(a, part, 1, a1);
-    a1.work = 0;
-    for (int32_t u = 0; u < a1.n_units; ++u) a1.unit_work0[u + 1] = a1.work += (uint32_t)r->tiles[0];
-    const rip::policy::WidePlan plan = rip::policy::wide_plan(kmax, a1.work, bf16, mom, wide_act > 0);
-    for (int32_t u = 0; u < a1.n_units; ++u) {
-      const int k = (int)rip::unit_info_k(a1.unit_info[u]);
-      a1.unit_info[u] = rip::unit_info_pack(rip::unit_info_base(a1.unit_info[u]), (uint32_t)k,
-                                            (uint32_t)rip::policy::wide_share(k, plan.waves));
-    }
-    return launch(a1, plan.waves, plan.per_cu);
   }
-  // One launch, or two when the units of a long step want residency caps far
-  // apart (and no cap is forced).
-  int w0 = 0, w1 = 0;
-  if (forced_bpc == 0 &&
-      rip::policy::long_enough_to_split(rip::policy::step_bytes(shapes.k, shapes.act, shapes.n, mom,
-                                                                r->stream_bytes)) &&
-      rip::policy::split_units(shapes.k, shapes.act, shapes.n, mom, part, &w0, &w1, segs)) {
-    subset_step(a, part, 0, a0);
-    subset_step(a, part, 1, a1);
-    if ((rc = launch(a0, 0, w0)) != RIP_OK) return rc;
-    return launch(a1, 0, w1);
+  if (n_wide == 0) return RIP_OK;
+  subset_step(a, part, 2, a1);
+  a1.work = 0;
+  for (int32_t u = 0; u < a1.n_units; ++u) a1.unit_work0[u + 1] = a1.work += (uint32_t)r->tiles[0];
+  const rip::policy::WidePlan plan = rip::policy::wide_plan(kmax, a1.work, bf16, mom, wide_act > 0);
+  for (int32_t u = 0; u < a1.n_units; ++u) {
+    const int k = (int)rip::unit_info_k(a1.unit_info[u]);
+    a1.unit_info[u] = rip::unit_info_pack(rip::unit_info_base(a1.unit_info[u]), (uint32_t)k,
+                                          (uint32_t)rip::policy::wide_share(k, plan.waves));
   }
-  return launch(a, 0, rip::policy::launch_waves(shapes.k, shapes.act, shapes.n, mom, segs));
+  return launch(a1, plan.waves, plan.per_cu);
 }
 
 extern "C" int32_t rip_step(rip_sched* s, const rip_replicas* r, int64_t step,

@@ -228,6 +228,24 @@ def test_split_launches_global_division(dtype, mom):
                          f"split dtype={dtype} mom={mom}")
 
 
+@pytest.mark.parametrize("dtype,mom", [(DTYPE_F32, 0.9), (DTYPE_F32, 0.0), (DTYPE_BF16, 0.9)])
+def test_split_beside_a_group_above_eight(dtype, mom):
+    """A long step with a group above eight, groups of eight and small units:
+    the group on its own kernel, the others in two launches; a short one in two
+    launches altogether, and a small one in one."""
+    table = [[tuple(range(12)), tuple(range(12, 20)), tuple(range(20, 28)), (28, 29), (30, 31)]]
+    base = wl.Workload("beside", 34, [1], dtype, 0.1 if dtype == DTYPE_F32 else 20.0, mom, 0.01,
+                       dict(mode=wl.TABLE, table=table), 3, 27, grad_ring=1,
+                       param_sigma=1.0 if dtype == DTYPE_F32 else 0.05)
+    for P, launches in ((4099, 1), (300_007, 2), (6_000_011, 3)):
+        w = wl.scaled(base, [P])
+        log(f"case beside a wide group dtype={dtype} mom={mom} P={P}")
+        run = DeviceRun(w)
+        run.run(w.steps)
+        assert set(run.launches) == {launches}, run.launches
+        check_against_oracle(run, sample_windows(P, 12, 8192, 6), f"beside P={P} mom={mom}")
+
+
 def test_allreduce_and_max_replicas():
     """k = N = 256 (the largest handle): P-Reduce over every replica is the
     global mean; then pairs (AD-PSGD's k = 2)."""
