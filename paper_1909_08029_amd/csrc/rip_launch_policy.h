@@ -157,7 +157,8 @@ constexpr int wide_resident(bool bf16, bool mom) { return bf16 ? (mom ? 16 : 20)
 // above 64 per CU, time above the best plan of each, four members a wave on
 // eight or sixteen waves -> this plan: SGD, 13 to 24 members 3.3% -> 1.9, 25 to
 // 32 2.1 -> 0.8; averaging, 21 to 24 11 -> 0.9; momentum, 9 to 12 2.0 -> 0.8, 13
-// to 24 4.0 -> 1.2, 25 to 64 3.2 -> 1.2 (single waves that took the members in
+// to 24 4.0 -> 1.2, 25 to 64 3.2 -> 1.2, bf16 25 to 32 above 256 per CU, at four
+// waves, 0.8 -> 0.7, at three 2.2 (single waves that took the members in
 // chunks of eight, all workgroups capped at four per CU, 3 to 5%).  Between 16
 // and 64 per CU momentum gains (33 to 64 members 3.9%, 13 to 24 1.8%), SGD does
 // not (13 to 24 +0.0%, up to 8% slower).  Replicas at a pitch of a power of two
@@ -170,6 +171,7 @@ inline WidePlan wide_plan(int32_t kmax, int64_t work, bool bf16, bool mom, bool 
   WidePlan p;
   if (work > (mom || !updates ? kLongWide : 4 * kLongWide)) {
     if (mom) return kmax <= 12 ? WidePlan{2, 6} : kmax <= 24 ? WidePlan{2, 4}
+                  : kmax <= 32 && bf16 ? WidePlan{4, 2}
                   : kmax <= 64 ? WidePlan{3, 2} : WidePlan{kWideWaves, 1};
     if (kmax <= 12 || (updates && kmax <= 24)) return WidePlan{3, 4};
     if (kmax <= 32) return updates ? WidePlan{6, 2} : WidePlan{4, 4};
