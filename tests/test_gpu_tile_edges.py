@@ -1,11 +1,15 @@
 """Ends of segments around every tile size, bit for bit against the oracle.
 
-A tile is 64 lanes x 1-8 slots x 16 bytes of each member stream; a segment's
+A tile is 64 lanes x 1-4 slots x 16 bytes of each member stream; a segment's
 last tile holds fewer whole vectors and up to N - 1 single elements (N = 4
-fp32, 8 bf16).  Sizes step over each of those edges.  Every buffer lies
-between guard bytes that must not change, and one member of each group does
-not update.
+fp32, 8 bf16).  Sizes step over each of those edges: in small launches, which
+take one slot per lane for every unit, and in larger ones, where units of up
+to three members take two or four.  Every buffer lies between guard bytes that
+must not change, and one member of each group does not update.
 """
+import os
+import re
+
 import numpy as np
 import pytest
 
@@ -17,6 +21,15 @@ from gpu_util import compare, log
 pytestmark = pytest.mark.gpu
 
 GUARD = 512  # bytes before and after every segment
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+POLICY = os.path.join(HERE, "..", "paper_1909_08029_amd", "csrc", "rip_launch_policy.h")
+
+
+def _one_slot_work():
+    """Most one-slot tiles of a launch that takes one slot for every unit."""
+    with open(POLICY) as f:
+        return int(re.search(r"kOneSlotWork = (\d+);", f.read()).group(1))
 
 
 def _arrays(rng, n, sizes, bf16):
@@ -98,6 +111,31 @@ def test_segment_ends(bf16, mom, k):
     _check(bf16, mom, k, [64 * N + 3], wd=1e-2, nesterov=mom)
     if k > 1:
         _check(bf16, False, k, [64 * N + 3, 7], average=True)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("mom", [False, True])
+@pytest.mark.parametrize("k", [1, 2, 3])
+def test_segment_ends_of_several_slots(bf16, mom, k):
+    """Ends in every slot of a tile of two or four slots: segments of a few
+    tiles each beside one that makes the launch large enough for them, then
+    flat ranges that end in each slot (for bf16 on a lone element)."""
+    N = 8 if bf16 else 4
+    slot, tile = 64 * N, 64 * N * 4
+    units = 2                              # a group and a lone update, or two of those
+    base = tile * (-(-_one_slot_work() // (4 * units)) + 1)
+    edges = {1, N - 1, N, N + 1, 2 * N + 3, 2 * tile - 1, 2 * tile}
+    for u in range(1, 5):
+        edges |= {u * slot + d for d in (-N - 1, -N, -1, 0, 1, N - 1, N, N + 1)}
+        edges |= {tile + u * slot - 1, tile + u * slot + 1}
+    log(f"case slots bf16={bf16} mom={mom} k={k}: {len(edges)} segments after {base} elements")
+    flat = [base + u * slot + d for u in range(4) for d in (1, 32 * N + N + 1)]
+    for sizes in ([base] + sorted(edges), *([m] for m in flat)):
+        assert units * sum(-(-m // slot) for m in sizes) > _one_slot_work()
+        _check(bf16, mom, k, sizes)
+    _check(bf16, mom, k, [base + 3 * slot + 5, 2 * slot + 1], wd=1e-2, nesterov=mom)
+    if k > 1:
+        _check(bf16, False, k, [base + slot + 3, 2 * slot + 7], average=True)
 
 
 @pytest.mark.parametrize("bf16", [False, True])
