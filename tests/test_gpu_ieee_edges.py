@@ -43,7 +43,12 @@ LONE = [23, 24]
 # the first member of every group updates; a few others do not
 IDLE = {4, 13, 16, 19}
 ACTIVE = [r for r in range(N) if r not in IDLE]
-P = 9005   # several tiles of every unit shape, and an element-wise tail
+P = 9005   # several tiles of every unit shape, and a ragged tail
+# the step in one call, or the units of up to eight members in one and the
+# group of nine in another
+CALLS = {"together": [(GROUPS, ACTIVE)],
+         "apart": [(GROUPS[:4], [r for r in ACTIVE if r not in GROUPS[4]]),
+                   (GROUPS[4:], [r for r in ACTIVE if r in GROUPS[4]])]}
 
 
 @pytest.fixture(scope="module", autouse=True)
@@ -206,21 +211,24 @@ def from_device(rows, dtype):
 @pytest.mark.parametrize("momentum", [0.0, 0.9])
 @pytest.mark.parametrize("fused", [True, False])
 @pytest.mark.parametrize("dtype", [DTYPE_F32, DTYPE_BF16])
-def test_edge_values_match_oracle(dtype, fused, momentum, lr):
+@pytest.mark.parametrize("calls", CALLS)
+def test_edge_values_match_oracle(calls, dtype, fused, momentum, lr):
     import torch
     import paper_1909_08029_amd as rip
     from oracle import preduce as op
     seed = 1000 + 8 * dtype + 4 * int(fused) + 2 * int(momentum > 0) + int(lr == 1.0)
-    log(f"case ieee edges dtype={dtype} fused={fused} momentum={momentum} lr={lr} seed={seed}")
+    log(f"case ieee edges {calls} dtype={dtype} fused={fused} momentum={momentum} lr={lr} "
+        f"seed={seed}")
     w, g, v = edge_inputs(dtype, momentum, seed)
     dw, dg = to_device(w, dtype), to_device(g, dtype)
     dv = to_device(v, dtype) if momentum else None
     h = rip.Replicas(dw, dg, dv)
-    if fused:
-        rip.rip_preduce(h, GROUPS, ACTIVE, lr=lr, momentum=momentum)
-    else:
-        rip.rip_local_step(h, ACTIVE, lr, momentum)
-        rip.rip_preduce(h, GROUPS)
+    for groups, active in CALLS[calls]:
+        if fused:
+            rip.rip_preduce(h, groups, active, lr=lr, momentum=momentum)
+        else:
+            rip.rip_local_step(h, active, lr, momentum)
+            rip.rip_preduce(h, groups)
     torch.cuda.synchronize()
     dt = op.BF16 if dtype == DTYPE_BF16 else op.F32
     with np.errstate(over="ignore", invalid="ignore"):
@@ -253,7 +261,8 @@ def compare_nan_aware(gpu, ora, dtype, what):
 
 @pytest.mark.parametrize("wd,nesterov", [(1e-2, False), (1e-2, True), (0.0, True)])
 @pytest.mark.parametrize("dtype", [DTYPE_F32, DTYPE_BF16])
-def test_nan_inputs_and_decay_nesterov_edges(dtype, wd, nesterov):
+@pytest.mark.parametrize("calls", CALLS)
+def test_nan_inputs_and_decay_nesterov_edges(calls, dtype, wd, nesterov):
     """The kernel variant with weight decay and Nesterov momentum on the same
     edge values, plus NaN parameters and gradients scattered through the
     units: a NaN input makes its unit's mean NaN and nothing else, and
@@ -263,7 +272,7 @@ def test_nan_inputs_and_decay_nesterov_edges(dtype, wd, nesterov):
     import paper_1909_08029_amd as rip
     from oracle import preduce as op
     seed = 2000 + 8 * dtype + 2 * int(nesterov) + int(wd > 0)
-    log(f"case ieee nan dtype={dtype} wd={wd} nesterov={nesterov} seed={seed}")
+    log(f"case ieee nan {calls} dtype={dtype} wd={wd} nesterov={nesterov} seed={seed}")
     w, g, v = edge_inputs(dtype, 0.9, seed)
     rng = np.random.default_rng(seed)
     qnan = 0x7FC0 if dtype == DTYPE_BF16 else 0x7FC00000
@@ -276,7 +285,9 @@ def test_nan_inputs_and_decay_nesterov_edges(dtype, wd, nesterov):
         bits[pick] = (qnan | payload | sign)[pick]
     dw, dg, dv = to_device(w, dtype), to_device(g, dtype), to_device(v, dtype)
     h = rip.Replicas(dw, dg, dv)
-    rip.rip_preduce(h, GROUPS, ACTIVE, lr=0.5, momentum=0.9, weight_decay=wd, nesterov=nesterov)
+    for groups, active in CALLS[calls]:
+        rip.rip_preduce(h, groups, active, lr=0.5, momentum=0.9, weight_decay=wd,
+                        nesterov=nesterov)
     torch.cuda.synchronize()
     dt = op.BF16 if dtype == DTYPE_BF16 else op.F32
     with np.errstate(over="ignore", invalid="ignore"):
