@@ -2,7 +2,7 @@
 
 Small shapes are compared element by element over the whole buffers: sizes
 that span several tiles and end in a ragged tail, every specialized group
-size and the generic path, fp32 and bf16 storage, SGD and momentum, fused and
+size and groups above them, fp32 and bf16 storage, SGD and momentum, fused and
 unfused forms, flat and separately allocated segments.  The five paper-shaped
 workloads run at full size in the launch configuration the benchmark times,
 and are checked on sampled windows (exact, because the method is
@@ -63,31 +63,32 @@ SMALL_P = [1, 3, 4, 4097, 3 * 4096 + 5, 2 * 8192 + 13]
 
 @pytest.mark.parametrize("dtype", [DTYPE_F32, DTYPE_BF16])
 @pytest.mark.parametrize("P", SMALL_P)
-def test_every_group_size_small(dtype, P):
-    """One table row holding groups of sizes 1..9 (9 takes the generic path)
-    over 45 replicas plus 3 ungrouped workers; some members inactive."""
-    sizes = list(range(1, 10))
+@pytest.mark.parametrize("largest", [8, 9])
+def test_every_group_size_small(largest, dtype, P):
+    """One table row holding groups of sizes 1..8 (each on its specialized
+    path) or 1..9 (with a group above eight a step this small runs on its
+    kernel as a whole) and 3 ungrouped workers; some members inactive."""
     groups, start = [], 0
-    for k in sizes:
+    for k in range(1, largest + 1):
         groups.append(tuple(range(start, start + k)))
         start += k
     n = start + 3
     base = wl.Workload("small", n, [P], dtype, 0.1 if dtype == DTYPE_F32 else 50.0, 0.0,
                        0.01, dict(mode=wl.TABLE, table=[groups]), 3, 21,
                        straggler_every=2, param_sigma=1.0 if dtype == DTYPE_F32 else 0.05)
-    log(f"case all-k dtype={dtype} P={P}")
+    log(f"case all-k to {largest} dtype={dtype} P={P}")
     run = DeviceRun(base)
     run.run(base.steps)
-    check_against_oracle(run, full_windows(P), f"allk P={P}")
+    check_against_oracle(run, full_windows(P), f"allk {largest} P={P}")
 
 
 @pytest.mark.parametrize("dtype", [DTYPE_F32, DTYPE_BF16])
 @pytest.mark.parametrize("wd,nesterov,mom", [(0.0, False, 0.9), (1e-2, True, 0.9),
                                              (5e-3, False, 0.0)])
 def test_large_groups_with_optimizers(dtype, wd, nesterov, mom):
-    """Groups above the specialized sizes (9, 16 and 23 members: one, two and
-    three chunks of eight, a ragged last chunk) with momentum, weight decay
-    and Nesterov, some members not updating, over segments with ragged tails."""
+    """Groups above the specialized sizes (9, 16 and 23 members: shared by
+    several waves, evenly and with a smaller last share) with momentum, weight
+    decay and Nesterov, some members not updating, over segments with ragged tails."""
     table = [[tuple(range(0, 9)), tuple(range(9, 25)), tuple(range(25, 48))],
              [tuple(range(1, 48, 2)), tuple(range(0, 48, 2))]]
     w = wl.Workload("wide", 48, [3 * 4096 + 11, 2048, 9], dtype,
@@ -101,6 +102,30 @@ def test_large_groups_with_optimizers(dtype, wd, nesterov, mom):
         run.run(w.steps)
         assert any(len(g) > 8 for _, gs in run.schedule for g in gs)
         check_against_oracle(run, full_windows(w.numel), f"wide {layout}")
+
+
+@pytest.mark.parametrize("dtype", [DTYPE_F32, DTYPE_BF16])
+@pytest.mark.parametrize("mom", [0.9, 0.0])
+@pytest.mark.parametrize("k", [9, 13, 24, 25, 33, 64, 65])
+def test_large_groups_in_long_launches(k, mom, dtype):
+    """Groups above eight over more than 16 and 64 tiles per CU, where a
+    workgroup has fewer waves and more rounds; some members not updating, and
+    a step that only averages."""
+    import paper_1909_08029_amd as rip
+    N = 8 if dtype == DTYPE_BF16 else 4
+    for tiles in (16 * 256 + 1, 64 * 256 + 1):
+        P = 64 * N * tiles - 2 * N - 1
+        w = wl.Workload("long", k, [P], dtype, 0.1 if dtype == DTYPE_F32 else 20.0, mom, 0.01,
+                        dict(mode=wl.TABLE, table=[[tuple(range(k))]]), 2, 29, grad_ring=1,
+                        param_sigma=1.0 if dtype == DTYPE_F32 else 0.05)
+        log(f"case long wide k={k} dtype={dtype} mom={mom} P={P}")
+        run = DeviceRun(w)
+        group, everyone = [tuple(range(k))], list(range(k))
+        run.schedule = [(everyone[1:], group), ([], group), (everyone, group)]
+        for active, groups in run.schedule:
+            rip.rip_preduce(run.handles[0], groups, active, lr=w.lr if active else None,
+                            momentum=mom if active else 0.0)
+        check_against_oracle(run, sample_windows(P, 6, 4096, 8), f"long wide k={k}")
 
 
 @pytest.mark.parametrize("dtype", [DTYPE_F32, DTYPE_BF16])
@@ -121,8 +146,7 @@ def test_segments_with_momentum(dtype, layout):
 def test_many_small_separate_segments(dtype, mom):
     """Hundreds of separately allocated segments, most shorter than one tile
     (some empty, some a few elements, a few spanning several tiles): every
-    launch searches a long segment table and most work runs through the
-    element-wise tail path."""
+    launch searches a long segment table and most work is in ragged tiles."""
     rs = np.random.default_rng(33)
     segs = [int(x) for x in rs.choice([0, 1, 3, 17, 255, 700, 1031, 2048, 9000], size=300)]
     w = wl.scaled(wl.WORKLOADS[4], segs, steps=5, n=7, dtype=dtype, momentum=mom,
