@@ -217,6 +217,10 @@ int32_t rip_sched_worker(const rip_sched* s, int32_t worker, rip_worker_state* o
  * device and lie inside the allocation holding its first byte; the buffers a
  * step writes (param, mom) must not overlap any other registered segment.
  * Gradient segments may overlap each other (replicas may share a gradient).
+ * A step reads and writes the registered elements and nothing else, with one
+ * exception: of a bf16 segment (or flat range) of odd length it reads the
+ * whole aligned four bytes that hold the last element.  The two bytes after it
+ * lie in the same page; no result depends on them, and they are not written.
  * The handle copies the pointer table to device memory (one allocation,
  * freed by rip_replicas_destroy) on the current device; calls using it must
  * run with that device current.  Destroy only after the work that uses it

@@ -208,7 +208,7 @@ __device__ __forceinline__ float update(float w, float g, float& v, const Opt& o
   }
 }
 
-// Launch-wide values, read once per workgroup before anything else.
+// Launch-wide values, read once per work item before anything else.
 struct Header {
   const RIP_CONST uint64_t* ptab;
   const RIP_CONST int64_t *seg_numel, *seg_tile0;
@@ -562,8 +562,9 @@ __global__ __launch_bounds__(kBlock) void fused_step_kernel(StepArgs) {
 // the members in chunks of eight one after the other waited for every chunk's
 // loads by themselves and left most of the chip idle on small replicas: 256
 // bf16 replicas of 65,539 93.2 us, now 25.6; 64 fp32 of 10,000 21.8, now 7.0;
-// 9 fp32 of 4M 85.1, now 70.2; 32 fp32 of 25.6M 1757, now 1702 (5.8 TB/s);
-// groups of 12 to 16 of 8M and more are between 5% faster and 3% slower.  Four
+// 9 fp32 of 4M 85.1, now 70.2; 32 fp32 of 25.6M 1797, now 1750 (5.6 TB/s).
+// Launches of more than 256 workgroups per CU are 1-7% ahead of them, momentum
+// groups above 64 level; pitches of a power of two up to 20% behind.  Four
 // members a wave: with eight, the updated values of a bf16 wave take 150-185
 // VGPRs, and one workgroup fits a CU (64 bf16 of 2.5M 221 us, now 176); two or
 // four slots per lane helped only at one size in ten.

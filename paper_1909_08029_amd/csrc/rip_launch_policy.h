@@ -13,10 +13,9 @@ constexpr int kMaxK = 8;   // largest group size with a specialized kernel path
 constexpr int kCus = 256;  // compute units of an MI355X
 
 // Resident waves per CU at which each unit shape sustained the most HBM
-// bandwidth on MI355X, by group size k (entry 0: groups above kMaxK streamed
-// by single waves; their kernel takes wide_plan below instead), for units
-// whose members all update (plain SGD, momentum) and for units that only
-// average.  Measured with bench.py --sweep-caps (32 fp32 replicas of 25.6M
+// bandwidth on MI355X, by group size k (1 to kMaxK; larger groups have a kernel
+// of their own and take wide_plan below), for units whose members all update
+// (plain SGD, momentum) and for units that only average.  Measured with bench.py --sweep-caps (32 fp32 replicas of 25.6M
 // parameters, every unit of one size, even caps of 2-16 waves/CU, one process
 // per shape; two sessions on different machines agreed) and again in replayed
 // graphs on 14-16 replicas of 16.8M.  With the kernel's shorter way to a
@@ -35,9 +34,9 @@ constexpr int kCus = 256;  // compute units of an MI355X
 // CU's LDS), so only even caps are used.  bf16 units (8 replicas of 1.3G
 // parameters) peaked at the same caps within 2%, except averaging-only groups
 // of eight, which ran 5% faster at 6 than at 8 (fp32: equal).
-constexpr int kWavesSgd[kMaxK + 1] = {4, 10, 10, 8, 10, 8, 8, 6, 6};
-constexpr int kWavesMom[kMaxK + 1] = {4, 10, 10, 10, 8, 6, 4, 4, 4};
-constexpr int kWavesAvg[kMaxK + 1] = {6, 12, 12, 8, 12, 10, 8, 6, 6};
+constexpr int kWavesSgd[kMaxK + 1] = {0, 10, 10, 8, 10, 8, 8, 6, 6};
+constexpr int kWavesMom[kMaxK + 1] = {0, 10, 10, 10, 8, 6, 4, 4, 4};
+constexpr int kWavesAvg[kMaxK + 1] = {0, 12, 12, 8, 12, 10, 8, 6, 6};
 // Handles of several segments (separate layer tensors) need more waves for some
 // shapes: a wave first finds its segment, a chain of scalar loads that flat
 // replicas don't have, and lanes of a tensor's last tile have nothing to load.
@@ -58,11 +57,10 @@ constexpr int kWavesDefault = 8;
 // the averaging-only and all-updating preferences, interpolated by the share
 // of updating members.  `segs`: the handle has several segments.
 inline double unit_waves(int32_t k, int32_t act, bool mom, bool segs = false) {
-  const int idx = k <= kMaxK ? k : 0;
   const double f = (double)act / (double)k;
-  const int sgd = segs ? seg_waves_sgd(idx) : kWavesSgd[idx];
-  const int avg = segs ? seg_waves_avg(idx) : kWavesAvg[idx];
-  return f * (mom ? kWavesMom[idx] : sgd) + (1.0 - f) * avg;
+  const int sgd = segs ? seg_waves_sgd(k) : kWavesSgd[k];
+  const int avg = segs ? seg_waves_avg(k) : kWavesAvg[k];
+  return f * (mom ? kWavesMom[k] : sgd) + (1.0 - f) * avg;
 }
 
 // Cap of a launch running `units` units (unit u: k[u] members, act[u] of them

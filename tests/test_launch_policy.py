@@ -1,7 +1,6 @@
 """The launch residency policy (paper_1909_08029_amd/csrc/rip_launch_policy.h)
-on the CPU: single-shape launches take their table entry, groups above the
-specialized sizes use the chunked-path entry, mixed launches take the
-byte-weighted mean rounded up to an even cap (tests/native/launch_policy_test.cpp)."""
+on the CPU: single-shape launches take their table entry, mixed launches take
+the byte-weighted mean rounded up to an even cap (tests/native/launch_policy_test.cpp)."""
 import os
 import shutil
 import subprocess
