@@ -154,7 +154,7 @@ constexpr int wide_resident(bool bf16, bool mom) { return bf16 ? (mom ? 16 : 20)
 // 2900 workgroups per CU, both types), each timed with 10 to 30 plans; of those
 // above 64 per CU, time above the best plan of each, four members a wave on
 // eight or sixteen waves -> this plan: SGD, 13 to 24 members 3.3% -> 1.9, 25 to
-// 32 2.1 -> 0.8; averaging, 21 to 24 11 -> 0.9; momentum, 9 to 12 2.0 -> 0.8, 13
+// 28 2.6 -> 0.6 (31 and 32: six waves 0.7 behind eight); averaging, 21 to 24 11 -> 0.9; momentum, 9 to 12 2.0 -> 0.8, 13
 // to 24 4.0 -> 1.2, 25 to 64 3.2 -> 1.2, bf16 25 to 32 above 256 per CU, at four
 // waves, 0.8 -> 0.7, at three 2.2 (single waves that took the members in
 // chunks of eight, all workgroups capped at four per CU, 3 to 5%).  Between 16
@@ -172,7 +172,7 @@ inline WidePlan wide_plan(int32_t kmax, int64_t work, bool bf16, bool mom, bool 
                   : kmax <= 32 && bf16 ? WidePlan{4, 2}
                   : kmax <= 64 ? WidePlan{3, 2} : WidePlan{kWideWaves, 1};
     if (kmax <= 12 || (updates && kmax <= 24)) return WidePlan{3, 4};
-    if (kmax <= 32) return updates ? WidePlan{6, 2} : WidePlan{4, 4};
+    if (kmax <= (updates ? 28 : 32)) return updates ? WidePlan{6, 2} : WidePlan{4, 4};
     return WidePlan{kWideWaves / 2, 2};
   }
   const int most = work <= kCus || (mom && kmax > 64) ? kWideWaves : kWideWaves / 2;
