@@ -289,9 +289,9 @@ __device__ __forceinline__ void load_members(const Header& h, uint64_t ids, uint
 // replicas of 304,327 with momentum, weight decay and groups of four 20.5 us
 // a step, now 19.1, and 18.4 with a size that ends on a tile; the same as 59
 // separate tensors 21.7, now 20.0.)
-template <int K, int U, bool BF16, bool MOM, bool EXT>
+template <int K, int U, bool BF16, bool MOM, bool EXT, bool PACE>
 __device__ __forceinline__ void tile_slots(Members& m, int64_t tile_byte, int bytes,
-                                           const Opt& o, int small) {
+                                           const Opt& o) {
   using V = Vec<BF16>;
   constexpr int N = V::N;
   constexpr float inv_k = (float)(1.0 / K);
@@ -361,17 +361,11 @@ __device__ __forceinline__ void tile_slots(Members& m, int64_t tile_byte, int by
   // to back they cost the HBM3E rate: 16 cycles between them gave groups of
   // six to eight of 25.6M to 276M elements 0.3-1.5% (eight of 138.4M fp32
   // 7546 -> 7475 us); with fewer streams the pause itself costs (groups of
-  // eight without momentum -2%, lone updates with it -2%).  So it does in a
-  // launch small enough for one-slot tiles, which leaves HBM idle: up to 512
-  // tiles 5-10% (two groups of eight of 16,384 3.40 us with it, 3.27 skipping
-  // it, 3.20 without any of this; bf16 3.89, 3.70 and 3.57), at 1024 nothing,
-  // beyond that it is ahead.  The branch is inside the asm: one of the
-  // compiler's ends the block, and it sank arithmetic below the stores.
-  const auto pace = [small] {
-    (void)small;
-    if constexpr (MOM && K >= 6) {
+  // eight without momentum -2%, lone updates with it -2%).
+  const auto pace = [] {
+    if constexpr (PACE) {
       __builtin_amdgcn_sched_barrier(0);
-      asm volatile("s_cmp_lg_u32 %0, 0\n\ts_cbranch_scc1 1f\n\ts_nop 15\n1:" ::"s"(small) : "scc");
+      asm volatile("s_nop 15");
       __builtin_amdgcn_sched_barrier(0);
     }
   };
@@ -479,7 +473,7 @@ __device__ __forceinline__ Place find_place(const Header& h, int O, int64_t tile
 // One tile of a unit of K members.  The tile geometry is a compile-time constant here, so a
 // workgroup reaches its first vector load after a handful of scalar
 // instructions: a flat handle needs no segment search at all.
-template <int K, int O, bool BF16, bool MOM, bool EXT>
+template <int K, int O, bool BF16, bool MOM, bool EXT, bool PACE>
 __device__ __forceinline__ void tile_of(const Header& h, const Unit& u, int64_t tile) {
   constexpr int SL = 1 << O;
   constexpr int N = Vec<BF16>::N;
@@ -488,19 +482,24 @@ __device__ __forceinline__ void tile_of(const Header& h, const Unit& u, int64_t 
   constexpr int esize = BF16 ? 2 : 4;
   Members m;
   load_members<K, MOM>(h, u.ids, u.act8, at.seg, m);
-  tile_slots<K, SL, BF16, MOM, EXT>(m, at.e_tile * esize, at.elems * esize, h.opt,
-                                     h.one_slot);
+  tile_slots<K, SL, BF16, MOM, EXT, PACE>(m, at.e_tile * esize, at.elems * esize, h.opt);
 }
+// A launch small enough for one-slot tiles leaves HBM idle, and the pause
+// between the stores of large momentum groups only costs there: up to 512 tiles
+// 5-10%, at 1024 nothing (two groups of eight of 16,384: 3.40 us with it, 3.20
+// without; bf16 3.89 and 3.57).  Such a launch has code of its own (3.27 us,
+// bf16 3.57); a branch over each pause took back half of it for bf16.
 template <int K, bool BF16, bool MOM, bool EXT>
 __device__ __forceinline__ void unit_tile(const Header& h, const Unit& u, int64_t tile) {
   constexpr int O = slot_log2(K, MOM);
-  if constexpr (O > 0) {
+  constexpr bool kPace = MOM && K >= 6;
+  if constexpr (O > 0 || kPace) {
     if (h.one_slot) {
-      tile_of<K, 0, BF16, MOM, EXT>(h, u, tile);
+      tile_of<K, 0, BF16, MOM, EXT, false>(h, u, tile);
       return;
     }
   }
-  tile_of<K, O, BF16, MOM, EXT>(h, u, tile);
+  tile_of<K, O, BF16, MOM, EXT, kPace>(h, u, tile);
 }
 
 template <bool BF16, bool MOM, bool EXT>

@@ -9,8 +9,8 @@ rip_kernels.hip to AMDGPU assembly with the library's own flags).
 * no fused multiply-add or multiply-accumulate is emitted: every product and
   sum rounds on its own, in the order the oracle follows;
 * no packed fp32 arithmetic is emitted (the library is built without it);
-* the pause between the stores of large momentum groups is skipped by a branch
-  (small launches do not take it);
+* the pause between the stores of large momentum groups is in one of two copies
+  of their code (small launches run the other);
 * the registers of the kernel of groups above eight hold the waves per CU that
   the launch policy counts on.
 """
@@ -69,11 +69,18 @@ def test_no_packed_fp32_arithmetic(asm):
     assert not {i for i in ins if i.startswith("v_pk_") and i.endswith("_f32")}
 
 
-def test_the_pause_between_stores_is_conditional(asm):
-    lines = [l.strip() for l in asm.splitlines()]
-    at = [i for i, l in enumerate(lines) if l == "s_nop 15"]
-    assert at
-    assert all(lines[i - 1].startswith("s_cbranch") for i in at)
+def test_small_launches_store_without_the_pause(asm):
+    """Units of k members store 2k vectors a slot with momentum.  Tiles: four
+    slots and one for k = 1, two and one for k = 2, one for k = 3 to 5, and for
+    k = 6 to 8 one with a pause after each store and one without."""
+    kernels = re.findall(r"^_ZN\S*fused_step_kernelILb\dELb1ELb\dE\S*:\s(.*?)\.end_amdhsa_kernel", asm,
+                         flags=re.S | re.M)
+    assert len(kernels) == 4
+    paced = sum(2 * k for k in (6, 7, 8))
+    for k in kernels:
+        assert len(re.findall(r"\bs_nop 15\b", k)) == paced
+        assert len(re.findall(r"\bbuffer_store_dwordx4\b", k)) == \
+            (8 + 2) + (8 + 4) + sum(2 * k for k in (3, 4, 5)) + 2 * paced
 
 
 def test_waves_of_the_wide_kernel_that_registers_hold(asm):
