@@ -600,12 +600,13 @@ extern "C" int32_t rip_preduce(const rip_replicas* r, const int32_t* group_offse
   // Groups above kMaxK run on a kernel of their own, unless one launch of all
   // units on that kernel is small.
   uint8_t part[RIP_MAX_REPLICAS];  // 0, 1: launches of up to kMaxK members; 2: groups above
-  int32_t n_wide = 0, wide_act = 0, kmax = 0;
+  int32_t n_wide = 0, wide_act = 0, wide_members = 0, kmax = 0;
   for (int32_t u = 0; u < shapes.n; ++u) {
     const bool wide = shapes.k[u] > rip::kMaxK;
     part[u] = wide ? 2 : 0;
     n_wide += wide;
     wide_act += wide ? shapes.act[u] : 0;
+    wide_members += wide ? shapes.k[u] : 0;
     kmax = std::max(kmax, shapes.k[u]);
   }
   const int64_t all_work = shapes.n * r->tiles[0];
@@ -647,7 +648,8 @@ extern "C" int32_t rip_preduce(const rip_replicas* r, const int32_t* group_offse
   subset_step(a, part, 2, a1);
   a1.work = 0;
   for (int32_t u = 0; u < a1.n_units; ++u) a1.unit_work0[u + 1] = a1.work += (uint32_t)r->tiles[0];
-  const rip::policy::WidePlan plan = rip::policy::wide_plan(kmax, a1.work, bf16, mom, wide_act > 0);
+  const rip::policy::WidePlan plan = rip::policy::wide_plan(
+      kmax, a1.work, bf16, mom, rip::policy::wide_updates(kmax, wide_act, wide_members));
   for (int32_t u = 0; u < a1.n_units; ++u) {
     const int k = (int)rip::unit_info_k(a1.unit_info[u]);
     a1.unit_info[u] = rip::unit_info_pack(rip::unit_info_base(a1.unit_info[u]), (uint32_t)k,

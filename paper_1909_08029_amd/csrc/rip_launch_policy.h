@@ -134,6 +134,20 @@ struct WidePlan {
 // Waves of the wide kernel that a CU's registers hold (61, 77, 86 and 104 VGPRs).
 constexpr int wide_resident(bool bf16, bool mom) { return bf16 ? (mom ? 16 : 20) : (mom ? 24 : 32); }
 
+// Whether `act` of a launch's `members` are enough updating ones for the plan of
+// updating groups; else most streams are read and written only, which the
+// averaging plan suits (All-Reduce with a straggler: one of 32 fp32 replicas of
+// 25.6M updating, with momentum: 1344 us at three waves, 1193 at eight).  Over
+// 37,000 random launches, the updating plan against the averaging one, above 16
+// workgroups per CU, a sixth updating or fewer: momentum, 9 to 16 members +4 to
+// +6% time, 17 to 20 +5, 25 +18 to +20, 28 to 32 +8 to +12, 33 to 64 +6; SGD, 13
+// to 16 +5, 25 to 28 +6 to +8; with a third updating 9 to 24 with momentum -2 to
+// -4%, 25 to 32 +1 to +5 up to two fifths.  (More than 64 with momentum up to 4
+// per CU: +31% on sixteen waves, one or none in ten updating.)
+inline bool wide_updates(int32_t kmax, int64_t act, int64_t members) {
+  return act * 5 > members * (kmax > 24 && kmax <= 32 ? 2 : 1);
+}
+
 // Short launches, up to 16 workgroups per CU (SGD: 64): four members per wave
 // as far as the waves go: eight waves, or sixteen when every workgroup has a CU
 // to itself, where only the latency of a workgroup counts (256 bf16 replicas of
@@ -154,10 +168,12 @@ constexpr int wide_resident(bool bf16, bool mom) { return bf16 ? (mom ? 16 : 20)
 // 2900 workgroups per CU, both types), each timed with 10 to 30 plans; of those
 // above 64 per CU, time above the best plan of each, four members a wave on
 // eight or sixteen waves -> this plan: SGD, 13 to 24 members 3.3% -> 1.9, 25 to
-// 28 2.6 -> 0.6 (31 and 32: six waves 0.7 behind eight); averaging, 21 to 24 11 -> 0.9; momentum, 9 to 12 2.0 -> 0.8, 13
-// to 24 4.0 -> 1.2, 25 to 64 3.2 -> 1.2, bf16 25 to 32 above 256 per CU, at four
-// waves, 0.8 -> 0.7, at three 2.2 (single waves that took the members in
-// chunks of eight, all workgroups capped at four per CU, 3 to 5%).  Between 16
+// 28 2.6 -> 0.6 (31 and 32: six waves 0.7 behind eight); averaging, 21 to 24
+// 11 -> 0.9; momentum, 9 to 12 2.0 -> 0.8, 13 to 24 4.0 -> 1.2, 25 to 64
+// 3.2 -> 1.2, bf16 25 to 32 above 256 per CU, at four waves, 0.8 -> 0.7, at
+// three 2.2 (single waves that took the members in chunks of eight, all
+// workgroups capped at four per CU, 3 to 5%).  Averaging, 28 to 32, stays as in
+// short launches (four waves, four workgroups to a CU: +1 to +3%).  Between 16
 // and 64 per CU momentum gains (33 to 64 members 3.9%, 13 to 24 1.8%), SGD does
 // not (13 to 24 +0.0%, up to 8% slower).  Replicas at a pitch of a power of two
 // (64 MiB and more) stay up to 20% behind those single waves.
@@ -168,14 +184,15 @@ constexpr int64_t kLongWide = 16 * kCus;  // workgroups
 inline WidePlan wide_plan(int32_t kmax, int64_t work, bool bf16, bool mom, bool updates) {
   WidePlan p;
   if (work > (mom || !updates ? kLongWide : 4 * kLongWide)) {
-    if (mom) return kmax <= 12 ? WidePlan{2, 6} : kmax <= 24 ? WidePlan{2, 4}
-                  : kmax <= 32 && bf16 ? WidePlan{4, 2}
-                  : kmax <= 64 ? WidePlan{3, 2} : WidePlan{kWideWaves, 1};
+    if (mom && updates)
+      return kmax <= 12 ? WidePlan{2, 6} : kmax <= 24 ? WidePlan{2, 4}
+             : kmax <= 32 && bf16 ? WidePlan{4, 2}
+             : kmax <= 64 ? WidePlan{3, 2} : WidePlan{kWideWaves, 1};
     if (kmax <= 12 || (updates && kmax <= 24)) return WidePlan{3, 4};
-    if (kmax <= (updates ? 28 : 32)) return updates ? WidePlan{6, 2} : WidePlan{4, 4};
-    return WidePlan{kWideWaves / 2, 2};
+    if (kmax <= (updates ? 28 : 27)) return updates ? WidePlan{6, 2} : WidePlan{4, 4};
+    if (updates || kmax > 32) return WidePlan{kWideWaves / 2, 2};
   }
-  const int most = work <= kCus || (mom && kmax > 64) ? kWideWaves : kWideWaves / 2;
+  const int most = work <= kCus || (mom && updates && kmax > 64) ? kWideWaves : kWideWaves / 2;
   p.waves = (kmax + kWideC - 1) / kWideC;
   if (p.waves > most) p.waves = most;
   const auto even = [](int64_t n) { return n < 2 ? n : (n + 1) / 2 * 2; };

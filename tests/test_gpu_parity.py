@@ -106,11 +106,11 @@ def test_large_groups_with_optimizers(dtype, wd, nesterov, mom):
 
 @pytest.mark.parametrize("dtype", [DTYPE_F32, DTYPE_BF16])
 @pytest.mark.parametrize("mom", [0.9, 0.0])
-@pytest.mark.parametrize("k", [9, 13, 24, 25, 33, 64, 65])
+@pytest.mark.parametrize("k", [9, 13, 24, 25, 28, 33, 64, 65])
 def test_large_groups_in_long_launches(k, mom, dtype):
     """Groups above eight over more than 16 and 64 tiles per CU, where a
-    workgroup has fewer waves and more rounds; some members not updating, and
-    a step that only averages."""
+    workgroup has fewer waves and more rounds; some members not updating, all
+    but one not, and a step that only averages."""
     import paper_1909_08029_amd as rip
     N = 8 if dtype == DTYPE_BF16 else 4
     for tiles in (16 * 256 + 1, 64 * 256 + 1):
@@ -121,7 +121,7 @@ def test_large_groups_in_long_launches(k, mom, dtype):
         log(f"case long wide k={k} dtype={dtype} mom={mom} P={P}")
         run = DeviceRun(w)
         group, everyone = [tuple(range(k))], list(range(k))
-        run.schedule = [(everyone[1:], group), ([], group), (everyone, group)]
+        run.schedule = [(everyone[1:], group), ([], group), (everyone, group), ([k // 2], group)]
         for active, groups in run.schedule:
             rip.rip_preduce(run.handles[0], groups, active, lr=w.lr if active else None,
                             momentum=mom if active else 0.0)
