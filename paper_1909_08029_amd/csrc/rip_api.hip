@@ -611,7 +611,7 @@ extern "C" int32_t rip_preduce(const rip_replicas* r, const int32_t* group_offse
   }
   const int64_t all_work = shapes.n * r->tiles[0];
   if (n_wide > 0 && all_work <= rip::policy::kLongWide &&
-      all_work * rip::policy::wide_plan(kmax, all_work, bf16, mom, true).waves <=
+      all_work * rip::policy::wide_plan(kmax, all_work, bf16, mom, 1.0).waves <=
           rip::policy::kWideAllWaves) {
     std::memset(part, 2, sizeof part);
     n_wide = shapes.n;
@@ -649,7 +649,7 @@ extern "C" int32_t rip_preduce(const rip_replicas* r, const int32_t* group_offse
   a1.work = 0;
   for (int32_t u = 0; u < a1.n_units; ++u) a1.unit_work0[u + 1] = a1.work += (uint32_t)r->tiles[0];
   const rip::policy::WidePlan plan = rip::policy::wide_plan(
-      kmax, a1.work, bf16, mom, rip::policy::wide_updates(kmax, wide_act, wide_members));
+      kmax, a1.work, bf16, mom, (double)wide_act / (double)wide_members);
   for (int32_t u = 0; u < a1.n_units; ++u) {
     const int k = (int)rip::unit_info_k(a1.unit_info[u]);
     a1.unit_info[u] = rip::unit_info_pack(rip::unit_info_base(a1.unit_info[u]), (uint32_t)k,

@@ -134,20 +134,6 @@ struct WidePlan {
 // Waves of the wide kernel that a CU's registers hold (61, 77, 86 and 104 VGPRs).
 constexpr int wide_resident(bool bf16, bool mom) { return bf16 ? (mom ? 16 : 20) : (mom ? 24 : 32); }
 
-// Whether `act` of a launch's `members` are enough updating ones for the plan of
-// updating groups; else most streams are read and written only, which the
-// averaging plan suits (All-Reduce with a straggler: one of 32 fp32 replicas of
-// 25.6M updating, with momentum: 1344 us at three waves, 1193 at eight).  Over
-// 37,000 random launches, the updating plan against the averaging one, above 16
-// workgroups per CU, a sixth updating or fewer: momentum, 9 to 16 members +4 to
-// +6% time, 17 to 20 +5, 25 +18 to +20, 28 to 32 +8 to +12, 33 to 64 +6; SGD, 13
-// to 16 +5, 25 to 28 +6 to +8; with a third updating 9 to 24 with momentum -2 to
-// -4%, 25 to 32 +1 to +5 up to two fifths.  (More than 64 with momentum up to 4
-// per CU: +31% on sixteen waves, one or none in ten updating.)
-inline bool wide_updates(int32_t kmax, int64_t act, int64_t members) {
-  return act * 5 > members * (kmax > 24 && kmax <= 32 ? 2 : 1);
-}
-
 // Short launches, up to 16 workgroups per CU (SGD: 64): four members per wave
 // as far as the waves go: eight waves, or sixteen when every workgroup has a CU
 // to itself, where only the latency of a workgroup counts (256 bf16 replicas of
@@ -172,24 +158,42 @@ inline bool wide_updates(int32_t kmax, int64_t act, int64_t members) {
 // 11 -> 0.9; momentum, 9 to 12 2.0 -> 0.8, 13 to 24 4.0 -> 1.2, 25 to 64
 // 3.2 -> 1.2, bf16 25 to 32 above 256 per CU, at four waves, 0.8 -> 0.7, at
 // three 2.2 (single waves that took the members in chunks of eight, all
-// workgroups capped at four per CU, 3 to 5%).  Averaging, 28 to 32, stays as in
-// short launches (four waves, four workgroups to a CU: +1 to +3%).  Between 16
+// workgroups capped at four per CU, 3 to 5%).  Averaging, 28 to 32 up to 256
+// per CU, stays as in short launches (four waves, four workgroups: +1 to +3%).  Between 16
 // and 64 per CU momentum gains (33 to 64 members 3.9%, 13 to 24 1.8%), SGD does
 // not (13 to 24 +0.0%, up to 8% slower).  Replicas at a pitch of a power of two
 // (64 MiB and more) stay up to 20% behind those single waves.
 //
 // Workgroups per CU are even (an odd count gets the residency of the even one
 // below).
+//
+// `share`: the part of the members that update.  Up to a fifth, most streams are
+// read and written only, and the averaging plan suits them (All-Reduce with a
+// straggler: one of 32 fp32 replicas of 25.6M updating, with momentum: 1344 us at
+// three waves, 1193 at eight).  Over 37,000 random launches above 16 workgroups
+// per CU, time with the updating plan against the averaging one, a sixth updating
+// or fewer: momentum, 9 to 16 members +4 to +6%, 17 to 20 +5, 25 to 32 +8 to +20,
+// 33 to 64 +6; SGD, 13 to 16 +5, 25 to 28 +6 to +8; a third updating, 9 to 24 with
+// momentum -2 to -4%.  (More than 64 with momentum, up to 4 per CU: +31% on
+// sixteen waves, one or none in ten updating.)  Groups of 25 to 32 stay as in
+// short launches up to three quarters (half of them updating with momentum, tensors
+// allocated one by one, 64 to 256 per CU: 4 to 6% less time than on the updating
+// plan, more 2 to 5%).  From 256 per CU on averaging groups of 28 to 64 take three
+// waves (tensors one by one, against eight: 28 to 32 5% less, 33 to 64 2 to 4% less;
+// rows of one buffer 0 to 2%; between 64 and 256 the two layouts differ in sign).
 constexpr int64_t kLongWide = 16 * kCus;  // workgroups
-inline WidePlan wide_plan(int32_t kmax, int64_t work, bool bf16, bool mom, bool updates) {
+inline WidePlan wide_plan(int32_t kmax, int64_t work, bool bf16, bool mom, double share) {
   WidePlan p;
-  if (work > (mom || !updates ? kLongWide : 4 * kLongWide)) {
+  const bool updates = share > 0.2;
+  if (work > (mom || !updates ? kLongWide : 4 * kLongWide) &&
+      !(updates && share <= 0.75 && kmax > 24 && kmax <= 32)) {
     if (mom && updates)
       return kmax <= 12 ? WidePlan{2, 6} : kmax <= 24 ? WidePlan{2, 4}
              : kmax <= 32 && bf16 ? WidePlan{4, 2}
              : kmax <= 64 ? WidePlan{3, 2} : WidePlan{kWideWaves, 1};
     if (kmax <= 12 || (updates && kmax <= 24)) return WidePlan{3, 4};
     if (kmax <= (updates ? 28 : 27)) return updates ? WidePlan{6, 2} : WidePlan{4, 4};
+    if (!updates && kmax <= 64 && work > 16 * kLongWide) return WidePlan{3, 4};
     if (updates || kmax > 32) return WidePlan{kWideWaves / 2, 2};
   }
   const int most = work <= kCus || (mom && updates && kmax > 64) ? kWideWaves : kWideWaves / 2;

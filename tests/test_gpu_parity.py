@@ -108,12 +108,12 @@ def test_large_groups_with_optimizers(dtype, wd, nesterov, mom):
 @pytest.mark.parametrize("mom", [0.9, 0.0])
 @pytest.mark.parametrize("k", [9, 13, 24, 25, 28, 33, 64, 65])
 def test_large_groups_in_long_launches(k, mom, dtype):
-    """Groups above eight over more than 16 and 64 tiles per CU, where a
-    workgroup has fewer waves and more rounds; some members not updating, all
-    but one not, and a step that only averages."""
+    """Groups above eight over more than 16 and 64 tiles per CU (256 for one
+    size), where a workgroup has fewer waves and more rounds; some members not
+    updating, every second one, all but one, and a step that only averages."""
     import paper_1909_08029_amd as rip
     N = 8 if dtype == DTYPE_BF16 else 4
-    for tiles in (16 * 256 + 1, 64 * 256 + 1):
+    for tiles in (16 * 256 + 1, 64 * 256 + 1) + ((256 * 256 + 1,) if k == 33 else ()):
         P = 64 * N * tiles - 2 * N - 1
         w = wl.Workload("long", k, [P], dtype, 0.1 if dtype == DTYPE_F32 else 20.0, mom, 0.01,
                         dict(mode=wl.TABLE, table=[[tuple(range(k))]]), 2, 29, grad_ring=1,
@@ -121,7 +121,8 @@ def test_large_groups_in_long_launches(k, mom, dtype):
         log(f"case long wide k={k} dtype={dtype} mom={mom} P={P}")
         run = DeviceRun(w)
         group, everyone = [tuple(range(k))], list(range(k))
-        run.schedule = [(everyone[1:], group), ([], group), (everyone, group), ([k // 2], group)]
+        run.schedule = [(everyone[1:], group), ([], group), (everyone, group), ([k // 2], group),
+                        (everyone[::2], group)]
         for active, groups in run.schedule:
             rip.rip_preduce(run.handles[0], groups, active, lr=w.lr if active else None,
                             momentum=mom if active else 0.0)

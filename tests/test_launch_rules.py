@@ -43,18 +43,21 @@ int main() {
           CHECK(work <= kLongWide || !mom || p.waves * p.per_cu <= 16);
         }
       }
-  // a group with momentum of which few members update streams like one that
-  // averages: it takes that plan (as far as the registers hold its waves)
-  for (int k = kMaxK + 1; k <= 256; ++k) {
-    CHECK(!wide_updates(k, 0, k) && wide_updates(k, k, k) && wide_updates(k, k / 2, k));
-    CHECK(!wide_updates(k, 1, k) && !wide_updates(k, k / 8, k));
-    for (int64_t work : {16 * kCus + 1, 64 * kCus + 1, 1 << 20})
+  // a group with momentum of which up to a fifth of the members update streams
+  // like one that averages and takes that plan; 25 to 32 members of which some
+  // update, that of short launches
+  for (int k = kMaxK + 1; k <= 256; ++k)
+    for (int64_t work : {16 * kCus + 1, 64 * kCus + 1, 256 * kCus + 1, 1 << 20})
       for (int bf16 = 0; bf16 < 2; ++bf16) {
-        const WidePlan p = wide_plan(k, work, bf16, true, false);
-        const WidePlan q = wide_plan(k, work, bf16, false, false);
-        CHECK(p.waves == q.waves && p.per_cu == q.per_cu);
+        const WidePlan q = wide_plan(k, work, bf16, false, 0.0);
+        for (int act = 0; act <= k; ++act) {
+          const double share = (double)act / k;
+          const WidePlan p = wide_plan(k, work, bf16, true, share);
+          CHECK(p.waves >= 1 && p.per_cu >= 1 && p.waves * p.per_cu <= 16);
+          if (act * 5 <= k) CHECK(p.waves == q.waves && p.per_cu == q.per_cu);
+          if (k > 24 && k <= 32 && act * 5 > k && act * 4 <= k * 3) CHECK(p.waves == (k + 3) / 4);
+        }
       }
-  }
   // short launches: all workgroups at once up to 16 per CU whatever the units
   // prefer and whatever they store, and never a higher cap for a longer launch
   for (int cap = 2; cap <= 12; cap += 2)
