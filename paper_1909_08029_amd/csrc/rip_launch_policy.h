@@ -15,25 +15,26 @@ constexpr int kCus = 256;  // compute units of an MI355X
 // Resident waves per CU at which each unit shape sustained the most HBM
 // bandwidth on MI355X, by group size k (1 to kMaxK; larger groups have a kernel
 // of their own and take wide_plan below), for units whose members all update
-// (plain SGD, momentum) and for units that only average.  Measured with bench.py --sweep-caps (32 fp32 replicas of 25.6M
-// parameters, every unit of one size, even caps of 2-16 waves/CU, one process
-// per shape; two sessions on different machines agreed) and again in replayed
-// graphs on 14-16 replicas of 16.8M.  With the kernel's shorter way to a
-// wave's first load some shapes peak two waves lower than before (replicas of
-// 25.6M, before -> after: lone updates 781 -> 773 us at 12 -> 10, groups of
-// seven 1380 -> 1333 at 8 -> 6, with momentum 1747 -> 1716 and groups of six
-// 1475 -> 1464 at 6 -> 4; averaging only, triples 583 -> 572 at 10 -> 8).  A lane keeps one 16-byte load in
-// flight per slot of every stream it reads (w, plus g and v when the member
-// updates), so units that read more streams peak with fewer resident waves;
-// beyond that, more waves add outstanding requests without adding bandwidth
-// (GB/s, plain SGD group of eight at 6 / 8 / 10 waves: 6246 / 5937 / 5892;
-// momentum group of three at 4 / 6 / 8: 4697 / 5154 / 6028).  Where two caps
-// measured within 1%, the table takes the one that also suited the mixed
-// launches of the paper's schedules.  Odd caps measured the same as the even
-// cap below them (the LDS reservation appears to be granted per half of a
-// CU's LDS), so only even caps are used.  bf16 units (8 replicas of 1.3G
-// parameters) peaked at the same caps within 2%, except averaging-only groups
-// of eight, which ran 5% faster at 6 than at 8 (fp32: equal).
+// (plain SGD, momentum) and for units that only average.  Measured with bench.py
+// --sweep-caps (32 fp32 replicas of 25.6M parameters, every unit of one size,
+// even caps of 2-16 waves/CU, one process per shape; two sessions on different
+// machines agreed) and again in replayed graphs on 14-16 replicas of 16.8M.
+// With the kernel's shorter way to a wave's first load some shapes peak two
+// waves lower than before (replicas of 25.6M, before -> after: lone updates 781
+// -> 773 us at 12 -> 10, groups of seven 1380 -> 1333 at 8 -> 6, with momentum
+// 1747 -> 1716 and groups of six 1475 -> 1464 at 6 -> 4; averaging only, triples
+// 583 -> 572 at 10 -> 8).  A lane keeps one 16-byte load in flight per slot of
+// every stream it reads (w, plus g and v when the member updates), so units that
+// read more streams peak with fewer resident waves; beyond that, more waves add
+// outstanding requests without adding bandwidth (GB/s, plain SGD group of eight
+// at 6 / 8 / 10 waves: 6246 / 5937 / 5892; momentum group of three at 4 / 6 / 8:
+// 4697 / 5154 / 6028).  Where two caps measured within 1%, the table takes the
+// one that also suited the mixed launches of the paper's schedules.  Odd caps
+// measured the same as the even cap below them (the LDS reservation appears to
+// be granted per half of a CU's LDS), so only even caps are used.  bf16 units (8
+// replicas of 1.3G parameters) peaked at the same caps within 2%, except
+// averaging-only groups of eight, which ran 5% faster at 6 than at 8 (fp32:
+// equal).
 constexpr int kWavesSgd[kMaxK + 1] = {0, 10, 10, 8, 10, 8, 8, 6, 6};
 constexpr int kWavesMom[kMaxK + 1] = {0, 10, 10, 10, 8, 6, 4, 4, 4};
 constexpr int kWavesAvg[kMaxK + 1] = {0, 12, 12, 8, 12, 10, 8, 6, 6};
@@ -101,9 +102,10 @@ constexpr int kOneSlotWork = 1024;
 // Beyond, launches that prefer 8 take 12 up to 24 per CU (83 launches: 1.9%
 // above the best at 8, 1.6 at 12; 16 replicas of 304,327 in 59 tensors, groups
 // of four with momentum, 17.3 us and 16.9), and launches that prefer 10 take
-// 12 up to 80 per CU, or 48 for bf16 with momentum (524 launches of 16 to 80: 2.1% above the best at 10, 1.2 at 12,
-// 2.2 at 16; lone updates of 2.6M 39.0 us and 37.9; bf16 with momentum up to
-// 48: 2.0% and 0.7, from 48 to 80 1.1 and 1.6).  Plain lone updates, four slots
+// 12 up to 80 per CU, or 48 for bf16 with momentum (524 launches of 16 to 80:
+// 2.1% above the best at 10, 1.2 at 12, 2.2 at 16; lone updates of 2.6M 39.0 us
+// and 37.9; bf16 with momentum up to 48: 2.0% and 0.7, from 48 to 80 1.1 and
+// 1.6).  Plain lone updates, four slots
 // per wave and so the fewest waves, take 12 up to 220 per CU (61 launches of 90
 // to 220: 1.0% above the best at 10, 0.1 at 12; 35 of 220 to 400: 0.3 and 0.5).
 // The lower preferences hold as they are (333 launches of 16 to 80: 1.5%, at 12
